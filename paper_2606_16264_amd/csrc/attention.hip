@@ -293,9 +293,11 @@ __device__ __forceinline__ bool chunk_interior(int pi0, int page_end, int first_
 // (waves 0 and 1 the keys of the chunk's two pages, waves 2 and 3 their
 // values), and every wave reads its matrix-core fragments from there.  Keys
 // are stored [32][HD] with the 16-byte chunk c of key row j at c ^ ksw(j);
-// values page by page, [2 pages][HD][2 halves of 8 keys], with half h of dim
-// row d at h ^ ((d >> 3) & 1).  Both make the fragment reads (16 key rows, or
-// 16 dim rows, at one logical chunk) hit distinct bank groups.  A DMA
+// values page by page, [2 pages][HD][2 halves of 8 keys], unswizzled.  Both make
+// the 16 lanes that the LDS serves at a time ({0-3, 12-15, 20-23, 24-27} and so
+// on, not 16 consecutive ones) hit distinct bank groups: 4.2 clocks per read.
+// (Value halves swapped for odd groups of 8 dim rows, which is conflict-free for
+// 16 consecutive lanes, took 8.0.)  A DMA
 // instruction writes 1 KB of LDS in lane order, so each lane fetches the 16
 // bytes that belong at its position: a permutation within the page's rows
 // (and, for keys, within its 32-dim blocks), which keeps every copy a run of
@@ -420,11 +422,10 @@ __device__ __forceinline__ void prefill_item(const AttnParams& p, const AttnItem
       sel[i] = kb * (64 / lanes_per_row) >= 16;
       off[i] = (lc >> 2) * 512 + (j & 15) * 32 + (lc & 3) * 8;
     } else {
-      // values: [page][dim][2 halves of 8 keys], half h of dim row d stored
-      // at h ^ ((d >> 3) & 1)
+      // values: [page][dim][2 halves of 8 keys]
       const int vb = (kb - KB / 1024) * 1024 + lane * 16;  // byte in the value half
       const int d = (vb % (HD * 32)) / 32;
-      const int h = ((vb / 16) & 1) ^ ((d >> 3) & 1);
+      const int h = (vb / 16) & 1;
       sel[i] = (kb - KB / 1024) * 1024 >= HD * 32;
       off[i] = d * 16 + h * 8;
     }
@@ -451,8 +452,7 @@ __device__ __forceinline__ void prefill_item(const AttnParams& p, const AttnItem
 #pragma unroll
   for (int ds = 0; ds < ND; ds++)
     kaddr[ds] = (unsigned)(key0 * (HD * 2) + (((4 * ds + g4) ^ ksw<HD>(key0)) << 4));
-  const unsigned vaddr = (unsigned)(KB + (g4 >> 1) * (HD * 32) + col * 32 +
-                                    (((g4 & 1) ^ ((col >> 3) & 1)) << 4));
+  const unsigned vaddr = (unsigned)(KB + (g4 >> 1) * (HD * 32) + col * 32 + ((g4 & 1) << 4));
 
   // scores of chunk c from its keys in LDS: this lane's masked raw scores, their
   // max, and whether some lane of the wave is above its row's threshold

@@ -20,9 +20,8 @@
 //    (second phase) spread between them, so that a wave keeps the matrix core
 //    fed while it issues its memory instructions; one barrier per slice;
 //  - LDS rows are 64 bytes (32 bf16 of K); the 16-byte chunk c of row r is
-//    stored at c ^ swz(r), which makes the fragment reads of 16 consecutive
-//    rows hit 16 distinct bank groups (the LDS serves a 16-byte read for 16
-//    lanes at a time from 64 banks);
+//    stored at c ^ swz(r), which makes the 16 lanes that the LDS serves at a
+//    time hit 16 distinct bank groups (see swz);
 //  - tile order is XCD-aware: workgroup b runs on XCD b % 8, and each XCD is
 //    handed a contiguous run of tiles taken in M-grouped order, so that the
 //    tiles sharing an L2 also share A and B panels;
@@ -55,12 +54,19 @@ constexpr int kGroupM = 8;
 // and the MFMA fragments read by inline-assembly ds_read_b128, with every wait
 // placed by hand (the helpers in mx_device.h).
 
-// Chunk swizzle of LDS row r: 16-byte chunk c is stored at c ^ swz(r).  A
-// 16-lane phase of a fragment read (rows r0 .. r0 + 15, one logical chunk)
-// then touches 16 distinct bank groups of 16 bytes: row r sits in group
-// 4 (r % 4) + chunk of its 256 bytes, and swz takes all four values over
-// r >> 2 for each r % 4.  (The same holds for 8-row phases over 32 banks.)
-__device__ __forceinline__ int swz(int r) { return ((r >> 1) & 3) ^ ((r >> 3) & 1); }
+// Chunk swizzle of LDS row r: 16-byte chunk c is stored at c ^ swz(r).  The
+// LDS serves a 16-byte read for 16 lanes at a time from 64 banks, and those are
+// not 16 consecutive lanes but {0-3, 12-15, 20-23, 24-27} (then the same + 4 - 8
+// ... within the 32, and the upper 32 likewise): in a fragment read they hold
+// rows 0-3 and 12-15 at chunk c and rows 4-11 at chunk c ^ 1.  Row r sits in bank
+// group 4 (r % 4) + stored chunk, and with (r >> 1) & 3 those 16 are distinct: a
+// read takes 4.2 clocks (256 bytes per clock; measured with eight waves reading
+// back to back).  The swizzle that is conflict-free for 16 consecutive lanes,
+// ((r >> 1) & 3) ^ ((r >> 3) & 1), takes 8.0 clocks, and the 128 x 256 tiles, whose
+// 64 x 64 wave tiles read 64 KB per slice, were bound by it: 576 x 12288 x 4096
+// 64.3 -> 59.4 us, 2304 x 6144 x 4096 with 128 x 256 tiles 114 -> 106 us, 256 x 256
+// tiles (96 KB per slice of twice the products) 0-1%.
+__device__ __forceinline__ int swz(int r) { return (r >> 1) & 3; }
 
 __device__ __forceinline__ void tile_coords(int bid, int tiles_m, int tiles_n, int& tm, int& tn) {
   const int nt = tiles_m * tiles_n;
