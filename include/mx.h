@@ -262,8 +262,7 @@ mx_status mx_layer_step(const mx_batch* batch, const mx_layer_cfg* cfg, const vo
 mx_status mx_layer_workspace_offsets(const mx_batch* batch, const mx_layer_cfg* cfg,
                                      size_t off[5]);
 
-/* Device token map of the batch as the iteration computes it (the kernel that
- * every entry point runs first): tok_req[T], tok_pos[T] (int32) and
+/* Device token map of the batch as the iteration computes it: tok_req[T], tok_pos[T] (int32) and
  * tok_slot[T] (int64), device outputs. */
 mx_status mx_debug_token_map(const mx_batch* batch, const mx_attn_shape* shape, int32_t* tok_req,
                              int32_t* tok_pos, int64_t* tok_slot, void* ws, size_t ws_bytes,

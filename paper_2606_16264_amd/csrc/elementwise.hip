@@ -275,28 +275,69 @@ __global__ __launch_bounds__(256) void prologue_kernel(TokenMapArgs a, int map_b
 }
 
 // ---------------------------------------------------------------- KV append
+// One workgroup per run (the up to 16 new tokens of one page) and kAppendCols
+// columns of the [nkv][d] rows.  Bound by memory: each value is read and written
+// once.  Keys go straight from their rows to the blocked page, in the page's
+// order, so that a wave stores one contiguous kilobyte of it.  Values are turned
+// in LDS (rows in by token, 16 bytes per lane, columns out): a thread holds the
+// run's values of one column and stores them as 16-byte halves of the
+// transposed page's row where the run fills a half, one by one elsewhere.  (One
+// workgroup per token, as before, wrote 2 bytes of 16 different 32-byte rows'
+// worth of lines per token.)
+constexpr int kAppendCols = 256;
+
 __global__ __launch_bounds__(256) void kv_append_kernel(const uint16_t* __restrict__ k_new,
                                                         const uint16_t* __restrict__ v_new,
                                                         uint16_t* __restrict__ k_pool,
                                                         uint16_t* __restrict__ v_pool,
-                                                        const int64_t* __restrict__ tok_slot,
+                                                        const AppendRun* __restrict__ runs,
                                                         int nkv, int d) {
-  const int64_t t = blockIdx.x;
-  const int64_t slot = tok_slot[t];
-  const int64_t page = slot / 16;
-  const int s_in = (int)(slot % 16);
-  const int n = nkv * d;
-  const uint16_t* ks = k_new + t * n;
-  const uint16_t* vs = v_new + t * n;
-  // keys: 16-byte chunks; a key page is blocked by 32 dims, [d / 32][16][32]
-  for (int c = threadIdx.x; c < n / 8; c += blockDim.x) {
-    const int g = (c * 8) / d, e = (c * 8) % d;
-    *reinterpret_cast<u32x4*>(k_pool + (page * nkv + g) * 16 * d + (e / 32) * 512 + s_in * 32 +
-                              e % 32) = *reinterpret_cast<const u32x4*>(ks + c * 8);
+  // two more halves per row: the column reads of a wave then differ in bank by row too
+  __shared__ __attribute__((aligned(16))) uint16_t sv[16][kAppendCols + 8];
+  const u32x4 rw = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(runs + blockIdx.x));
+  const AppendRun run = __builtin_bit_cast(AppendRun, rw);
+  const int s0 = (int)(run.slot & 15);
+  const int64_t page = run.slot >> 4;
+  const int ncol = nkv * d;
+  const int c0 = blockIdx.y * kAppendCols, cols = min(kAppendCols, ncol - c0);
+  const int t = threadIdx.x;
+  const uint16_t* ks = k_new + (int64_t)run.tok * ncol + c0;
+  const uint16_t* vs = v_new + (int64_t)run.tok * ncol + c0;
+  // values: 8 columns of a token per thread (rows are whole multiples of 64 columns)
+#pragma unroll
+  for (int i = 0; i < 2; i++) {
+    const int row = (t >> 5) + 8 * i, c = 8 * (t & 31);
+    if (row < run.n && c < cols)
+      *reinterpret_cast<u32x4*>(&sv[s0 + row][c]) =
+          *reinterpret_cast<const u32x4*>(vs + (int64_t)row * ncol + c);
   }
-  for (int u = threadIdx.x; u < n; u += blockDim.x) {
-    const int g = u / d, e = u % d;
-    v_pool[((page * nkv + g) * d + e) * 16 + s_in] = vs[u];
+  // keys: piece p of 32-column block b is columns 8 (p % 4) .. + 7 of slot p / 4
+#pragma unroll
+  for (int i = 0; i < 2; i++) {
+    const int b = (t >> 6) + 4 * i, p = t & 63;
+    const int row = (p >> 2) - s0, c = 32 * b + 8 * (p & 3);
+    if (row >= 0 && row < run.n && c < cols) {
+      const int g = (c0 + 32 * b) / d, e0 = (c0 + 32 * b) % d;
+      *reinterpret_cast<u32x4*>(k_pool + (page * nkv + g) * (16 * d) + (e0 / 32) * 512 + p * 8) =
+          *reinterpret_cast<const u32x4*>(ks + (int64_t)row * ncol + c);
+    }
+  }
+  __syncthreads();
+  if (t >= cols) return;
+  // column c0 + t is dim (c0 + t) % d of head (c0 + t) / d: row page nkv d + c0 + t
+  uint16_t* dst = v_pool + (page * ncol + c0 + t) * 16;
+#pragma unroll
+  for (int h = 0; h < 2; h++) {
+    const int lo = max(s0, 8 * h), hi = min(s0 + run.n, 8 * h + 8);
+    if (hi - lo == 8) {
+      u32x4 w;
+#pragma unroll
+      for (int e = 0; e < 4; e++)
+        w[e] = (uint32_t)sv[lo + 2 * e][t] | ((uint32_t)sv[lo + 2 * e + 1][t] << 16);
+      *reinterpret_cast<u32x4*>(dst + 8 * h) = w;
+    } else {
+      for (int s = lo; s < hi; s++) dst[s] = sv[s][t];
+    }
   }
 }
 
@@ -430,10 +471,11 @@ hipError_t launch_reduce_residual_rmsnorm(const float* partial, int ksplit, cons
 }
 
 hipError_t launch_kv_append(const uint16_t* k_new, const uint16_t* v_new, uint16_t* k_pool,
-                            uint16_t* v_pool, const int64_t* tok_slot, int T, int nkv, int d,
-                            hipStream_t stream) {
-  if (T == 0) return hipSuccess;
-  kv_append_kernel<<<T, 256, 0, stream>>>(k_new, v_new, k_pool, v_pool, tok_slot, nkv, d);
+                            uint16_t* v_pool, const AppendRun* runs, int64_t n_runs, int nkv,
+                            int d, hipStream_t stream) {
+  if (n_runs == 0) return hipSuccess;
+  const dim3 grid((unsigned)n_runs, (nkv * d + kAppendCols - 1) / kAppendCols);
+  kv_append_kernel<<<grid, 256, 0, stream>>>(k_new, v_new, k_pool, v_pool, runs, nkv, d);
   return hipGetLastError();
 }
 

@@ -411,10 +411,8 @@ mx_status device_state(DeviceState** out) {
   return MX_OK;
 }
 
-// Packs the plan's metadata into a pinned staging buffer and enqueues its copy
-// into the workspace (a kernel that reads the buffer through its device
-// mapping).  A staging slot is rewritten or freed only after the event
-// recorded behind its previous copy has completed.
+// A staging buffer is rewritten or freed only after the event recorded behind
+// the last kernel that read it has completed.
 // Records the open group's event after its last upload (buffer `last`) on the
 // group's stream; every buffer of the group is then covered by it.
 hipError_t close_group(DeviceState* ds, int last) {
@@ -442,8 +440,11 @@ void pack_meta(const Plan& p, const Layout& L, const mx_attn_shape* s, float the
   for (int k = 0; k < d / 2; k++) inv[k] = std::pow((double)theta, -2.0 * k / d);
 }
 
-mx_status upload_meta(const Plan& p, const Layout& L, const mx_attn_shape* s, float theta,
-                      void* ws, hipStream_t stream) {
+// Runs pack(host) on a staging buffer of at least `bytes` and launch(device
+// view of it), a kernel on `stream` that reads the buffer, under the ring's
+// discipline.
+template <typename Pack, typename Launch>
+mx_status staged(size_t bytes, hipStream_t stream, Pack&& pack, Launch&& launch) {
   DeviceState* ds;
   mx_status st = device_state(&ds);
   if (st != MX_OK) return st;
@@ -460,14 +461,14 @@ mx_status upload_meta(const Plan& p, const Layout& L, const mx_attn_shape* s, fl
     e = hipEventSynchronize(ds->ev[ds->cover[i]]);
     if (e != hipSuccess) return hip_fail(e, "hipEventSynchronize");
   }
-  if (ds->cap[i] < L.meta_end) {
+  if (ds->cap[i] < bytes) {
     if (ds->buf[i]) {
       e = hipHostFree(ds->buf[i]);
       ds->buf[i] = ds->dbuf[i] = nullptr;
       ds->cap[i] = 0;
       if (e != hipSuccess) return hip_fail(e, "hipHostFree");
     }
-    const size_t cap = std::max<size_t>(L.meta_end * 2, 1 << 16);
+    const size_t cap = std::max<size_t>(bytes * 2, 1 << 16);
     e = hipHostMalloc(&ds->buf[i], cap, hipHostMallocMapped);
     if (e != hipSuccess) { ds->buf[i] = nullptr; ds->cap[i] = 0; return hip_fail(e, "hipHostMalloc"); }
     e = hipHostGetDevicePointer(&ds->dbuf[i], ds->buf[i], 0);
@@ -479,9 +480,9 @@ mx_status upload_meta(const Plan& p, const Layout& L, const mx_attn_shape* s, fl
     }
     ds->cap[i] = cap;
   }
-  pack_meta(p, L, s, theta, (char*)ds->buf[i]);
-  e = launch_upload(ds->dbuf[i], ws, L.meta_end, stream);
-  if (e != hipSuccess) return hip_fail(e, "metadata upload launch");
+  pack((char*)ds->buf[i]);
+  e = launch(ds->dbuf[i]);
+  if (e != hipSuccess) return hip_fail(e, "metadata launch");
   ds->used[i] = true;
   if (ds->group_first < 0) {
     ds->group_first = i;
@@ -492,6 +493,13 @@ mx_status upload_meta(const Plan& p, const Layout& L, const mx_attn_shape* s, fl
     if ((e = close_group(ds, i)) != hipSuccess) return hip_fail(e, "hipEventRecord");
   }
   return MX_OK;
+}
+
+mx_status upload_meta(const Plan& p, const Layout& L, const mx_attn_shape* s, float theta,
+                      void* ws, hipStream_t stream) {
+  return staged(
+      L.meta_end, stream, [&](char* h) { pack_meta(p, L, s, theta, h); },
+      [&](const void* dev) { return launch_upload(dev, ws, L.meta_end, stream); });
 }
 
 template <typename T>
@@ -731,19 +739,35 @@ MX_EXPORT mx_status mx_kv_append(const mx_batch* batch, const mx_attn_shape* sha
   if (T == 0) return MX_OK;
   if (!k_new || !v_new || !k_pool || !v_pool) return fail(MX_ERR_NULL, "tensor pointer is NULL");
   if ((st = check_aligned({k_new, v_new, k_pool, v_pool, ws})) != MX_OK) return st;
-  Plan p;
-  build_plan(batch, shape, false, p);
-  const Layout L = layout_for(p, shape, nullptr);
+  // one run per page that a request's new tokens touch
+  int64_t n_pages = 0, n_runs = 0;
+  for (int r = 0; r < batch->num_reqs; r++) {
+    const mx_request& q = batch->reqs[r];
+    n_pages += ceil_div((int64_t)q.ctx_len + q.n_new, 16);
+    n_runs += (q.ctx_len + q.n_new - 1) / 16 - q.ctx_len / 16 + 1;
+  }
+  const Layout L = make_layout(batch->num_reqs, T, n_pages, 0, 0, 0, shape, nullptr, 0);
   if ((st = check_ws(L, ws, ws_bytes)) != MX_OK) return st;
-  if ((st = upload_meta(p, L, shape, 1e4f, ws, stream)) != MX_OK) return st;
-  hipError_t e = launch_token_map(at<ReqDev>(ws, L.reqs), p.R, p.T, at<int32_t>(ws, L.pages),
-                                  at<int32_t>(ws, L.tok_req), at<int32_t>(ws, L.tok_pos),
-                                  at<int64_t>(ws, L.tok_slot), nullptr, nullptr, 0, stream);
-  if (e != hipSuccess) return hip_fail(e, "token map launch");
-  e = launch_kv_append(k_new, v_new, k_pool, v_pool, at<int64_t>(ws, L.tok_slot), p.T,
-                       shape->n_kv_heads, shape->head_dim, stream);
-  if (e != hipSuccess) return hip_fail(e, "kv append launch");
-  return MX_OK;
+  return staged(
+      n_runs * sizeof(AppendRun), stream,
+      [&](char* h) {
+        AppendRun* run = reinterpret_cast<AppendRun*>(h);
+        int32_t tok = 0;
+        for (int r = 0; r < batch->num_reqs; r++) {
+          const mx_request& q = batch->reqs[r];
+          const int end = q.ctx_len + q.n_new;
+          for (int pos = q.ctx_len; pos < end;) {
+            const int n = std::min(16 - pos % 16, end - pos);
+            *run++ = AppendRun{tok, n, (int64_t)q.pages[pos / 16] * 16 + pos % 16};
+            tok += n;
+            pos += n;
+          }
+        }
+      },
+      [&](const void* dev) {
+        return launch_kv_append(k_new, v_new, k_pool, v_pool, static_cast<const AppendRun*>(dev),
+                                n_runs, shape->n_kv_heads, shape->head_dim, stream);
+      });
 }
 
 MX_EXPORT mx_status mx_paged_attn(const mx_batch* batch, const mx_attn_shape* shape,

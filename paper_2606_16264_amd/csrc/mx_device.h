@@ -133,6 +133,13 @@ struct AttnItem {
   int32_t part;
 };
 
+// New tokens of one request that share a page: batch rows tok .. tok + n - 1 to
+// the slots slot .. slot + n - 1 (n <= 16, slot % 16 + n <= 16).
+struct AppendRun {
+  int32_t tok, n;
+  int64_t slot;
+};
+
 struct MergeItem {
   int32_t req;
   int32_t part_base;  // partial index of (req, q head 0, split 0)

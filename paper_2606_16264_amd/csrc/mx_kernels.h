@@ -75,10 +75,12 @@ hipError_t launch_reduce_residual_rmsnorm(const float* partial, int ksplit, cons
                                           uint16_t* x1, const uint16_t* g, uint16_t* h, int M,
                                           int H, float eps, int split_row, hipStream_t stream);
 
-// KV append of given k/v rows [T][nkv][d] into the pools.
+// KV append of given k/v rows [T][nkv][d] into the pools, one run per page that
+// new tokens touch.  The runs may lie in pinned host memory (its device mapping):
+// every workgroup reads one.
 hipError_t launch_kv_append(const uint16_t* k_new, const uint16_t* v_new, uint16_t* k_pool,
-                            uint16_t* v_pool, const int64_t* tok_slot, int T, int nkv, int d,
-                            hipStream_t stream);
+                            uint16_t* v_pool, const AppendRun* runs, int64_t n_runs, int nkv,
+                            int d, hipStream_t stream);
 
 // Gather of one request's keys/values (positions 0 .. len-1) into [len][nkv][d].
 hipError_t launch_gather(const uint16_t* k_pool, const uint16_t* v_pool, const int32_t* pages,

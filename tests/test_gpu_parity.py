@@ -107,6 +107,31 @@ def test_kv_append_bit_exact(nkv, d):
     np.testing.assert_array_equal(wdev.v_pool_canonical(v), ev)
 
 
+@pytest.mark.parametrize("nkv,d", [(1, 64), (5, 64), (3, 128), (40, 128)])
+def test_kv_append_page_runs(nkv, d):
+    """Chunks that start at every slot of a page and end at every slot, in rows of a part of, one
+    and several 256-column workgroups."""
+    say(f"case: kv append page runs nkv={nkv} d={d}")
+    rng = np.random.default_rng(40 + nkv)
+    cfg = wl.LayerConfig("t", 256, 256, nkv, nkv, d)
+    b = wl.custom_batch(rng, [15, 16, 17], [(1 + (7 * c) % 40, c) for c in range(16)]
+                        + [(n, 3) for n in range(1, 18)])
+    k, v = wdev.alloc_pools(cfg, b.pool_pages)
+    wdev.fill_pools(k, v, cfg, b, 7, poison=True)
+    sync()
+    k0, v0 = wdev.k_pool_canonical(k), wdev.v_pool_canonical(v)
+    kn = rng.integers(0, 65536, (b.T, nkv, d), dtype=np.uint16)
+    vn = rng.integers(0, 65536, (b.T, nkv, d), dtype=np.uint16)
+    mb = mx_batch(mx, b)
+    shape = mx_shape(mx, cfg, b.pool_pages)
+    mx.mx_kv_append(mb, shape, dev(kn), dev(vn), k, v,
+                    ws_tensor(mx.mx_workspace_bytes_for(mb, shape=shape)))
+    sync()
+    ek, ev = oracle.kv_append(b.n_new, b.ctx_len, b.page_tables, kn, vn, k0, v0)
+    np.testing.assert_array_equal(wdev.k_pool_canonical(k), ek)
+    np.testing.assert_array_equal(wdev.v_pool_canonical(v), ev)
+
+
 def test_gather_bit_exact():
     say("case: gather")
     rng = np.random.default_rng(31)
