@@ -765,24 +765,57 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
     decode_item<HD, false>(p, it, rq, smem);
 }
 
-// Deterministic merge of the key splits of one (decode request, q head).
+// Deterministic merge of the key splits of one (decode request, q head), a
+// workgroup each: HD / 4 threads hold a split's row, so 8 (HD = 128) or 16 splits
+// are read side by side, every load independent of the others (running maximum
+// per thread, the groups' states combined through LDS in group order).  Bound by
+// latency: 4.5 us for 33 splits (70B heads, four requests), where one thread per
+// dim that walked the splits twice in turn took 13.3 us.
+constexpr int kMergeThreads = 256;
 template <int HD>
-__global__ __launch_bounds__(HD) void attn_merge_kernel(AttnParams p, const MergeItem* merges) {
+__global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(AttnParams p,
+                                                                   const MergeItem* merges) {
+  constexpr int TPR = HD / 4, G = kMergeThreads / TPR;
+  __shared__ __attribute__((aligned(16))) float s_acc[G][HD];
+  __shared__ float s_m[G], s_l[G];
   const MergeItem mi = merges[blockIdx.x];
   const ReqDev rq = p.reqs[mi.req];
   const int h = blockIdx.y;
-  const int d = threadIdx.x;
+  const int g = threadIdx.x / TPR, d = 4 * (threadIdx.x % TPR);
   const int ns = rq.n_split;
   const int64_t base = (int64_t)mi.part_base + (int64_t)h * ns;
-  float M = kNegBig;
-  for (int s = 0; s < ns; s++) M = fmaxf(M, p.part_ml[(base + s) * 2]);
-  float L = 0.f, acc = 0.f;
-  for (int s = 0; s < ns; s++) {
-    const float w = exp2f(p.part_ml[(base + s) * 2] - M);
-    L += p.part_ml[(base + s) * 2 + 1] * w;
-    acc += p.part_o[(base + s) * HD + d] * w;
+  float m = kNegBig, l = 0.f;
+  f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int s = g; s < ns; s += G) {
+    const float2 ml = *reinterpret_cast<const float2*>(p.part_ml + (base + s) * 2);
+    const f32x4 o = *reinterpret_cast<const f32x4*>(p.part_o + (base + s) * HD + d);
+    const float mn = fmaxf(m, ml.x);
+    const float a = exp2f(m - mn), w = exp2f(ml.x - mn);
+    acc = acc * a + o * w;
+    l = l * a + ml.y * w;
+    m = mn;
   }
-  *out_ptr(p, rq.tok_start, h * HD + d) = f32_to_bf16(acc / L);
+  *reinterpret_cast<f32x4*>(&s_acc[g][d]) = acc;
+  if (d == 0) {
+    s_m[g] = m;
+    s_l[g] = l;
+  }
+  __syncthreads();
+  if (threadIdx.x >= HD / 2) return;
+  float M = kNegBig;
+#pragma unroll
+  for (int k = 0; k < G; k++) M = fmaxf(M, s_m[k]);
+  float L = 0.f, a0 = 0.f, a1 = 0.f;
+#pragma unroll
+  for (int k = 0; k < G; k++) {
+    const float w = exp2f(s_m[k] - M);  // a group without a split: 0 (some split has a key)
+    L += s_l[k] * w;
+    a0 += s_acc[k][2 * threadIdx.x] * w;
+    a1 += s_acc[k][2 * threadIdx.x + 1] * w;
+  }
+  *reinterpret_cast<uint32_t*>(out_ptr(p, rq.tok_start, h * HD + 2 * threadIdx.x)) =
+      pack_bf16x2(a0 / L, a1 / L);
 }
 
 }  // namespace
@@ -800,9 +833,9 @@ hipError_t launch_paged_attn(const AttnParams& p, int n_items, const MergeItem* 
   if (n_merges > 0) {
     dim3 grid(n_merges, p.nq);
     if (head_dim == 128)
-      attn_merge_kernel<128><<<grid, 128, 0, stream>>>(p, merges);
+      attn_merge_kernel<128><<<grid, kMergeThreads, 0, stream>>>(p, merges);
     else
-      attn_merge_kernel<64><<<grid, 64, 0, stream>>>(p, merges);
+      attn_merge_kernel<64><<<grid, kMergeThreads, 0, stream>>>(p, merges);
     return hipGetLastError();
   }
   return hipSuccess;

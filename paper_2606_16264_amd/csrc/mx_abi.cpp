@@ -135,21 +135,36 @@ struct Plan {
 };
 
 // Decode splits: about 1024 work items (the chip holds 512 attention
-// workgroups at once), at least 8 pages (four waves x two pages) per split.
+// workgroups at once), at least kMinSplitPages pages per split.
 // Fewer, longer items pay the start of an item (item, request and page-table
 // reads before its first keys arrive) less often, and a request that fits in
 // one split needs no partials and no merge: 2048 items were 3% slower on every
-// layer shape, 512 no faster.
+// layer shape, 512 no faster.  The same holds where there is too little work
+// for 1024 items: a batch whose decodes all have at most 32 pages runs them
+// whole, up to 64 pages when that still is an item per CU (calls of the
+// attention alone: 7B heads, one decode over 250 tokens 15.4 -> 12.4 us, 16 over
+// 700 tokens 35.9 -> 32.7; Llama-3-8B heads, 32 over 300-1000: 24.7 -> 20.2; but one
+// decode of 44 pages in one piece made the 7B layer 1% slower), and otherwise
+// splits have at least 16 pages, not the shortest possible 8 (70B heads, 8
+// decodes over 1000-2000 tokens: 18.8 -> 17.2 us).
+constexpr int64_t kMinSplitPages = 16, kUnsplitPages = 32, kUnsplitPagesFull = 64, kCUs = 256;
+
 int choose_split_pages(const mx_batch* b, const mx_attn_shape* s) {
   const int group = s->n_q_heads / s->n_kv_heads;
   const int64_t sub = s->n_kv_heads * ceil_div(group, 16);
-  int64_t total = 0;
+  int64_t total = 0, longest = 0, decodes = 0;
   for (int r = 0; r < b->num_reqs; r++)
-    if (b->reqs[r].phase == MX_DECODE)
-      total += ceil_div((int64_t)b->reqs[r].ctx_len + 1, 16) * sub;
+    if (b->reqs[r].phase == MX_DECODE) {
+      const int64_t pages = ceil_div((int64_t)b->reqs[r].ctx_len + 1, 16);
+      total += pages * sub;
+      longest = std::max(longest, pages);
+      decodes++;
+    }
   const int64_t target_items = 1024;
   int64_t sp = ceil_div(std::max<int64_t>(total, 1), target_items);
-  sp = std::max<int64_t>(8, std::min<int64_t>(sp, 4096));
+  sp = std::max(kMinSplitPages, std::min<int64_t>(sp, 4096));
+  const int64_t whole = decodes * sub >= kCUs ? kUnsplitPagesFull : kUnsplitPages;
+  if (longest <= whole) sp = std::max(sp, longest);
   sp = (sp + 1) / 2 * 2;
   return (int)sp;
 }
@@ -667,7 +682,8 @@ MX_EXPORT size_t mx_workspace_bytes(const mx_layer_cfg* cfg, const mx_attn_shape
     return 0;
   }
   const int64_t nq = shape->n_q_heads, nkv = shape->n_kv_heads, group = nq / nkv;
-  // every split has at least 8 pages, so splits <= pages / 8 + requests
+  // every split but a request's last has at least kMinSplitPages (more than 8)
+  // pages, so splits <= pages / 8 + requests
   const int64_t splits = max_pages / 8 + max_reqs;
   const int64_t items =
       splits * nkv * ceil_div(group, 16) + (max_tokens / kPrefillTileRows + max_reqs) * nq;

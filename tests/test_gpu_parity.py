@@ -268,6 +268,22 @@ def test_paged_attn_long_contexts_split(key):
     assert torch.equal(out, out2)
 
 
+@pytest.mark.parametrize("nq,nkv,d", [(8, 2, 128), (4, 4, 64)])
+@pytest.mark.parametrize("ctx", [[511, 5], [512, 5], [1023] * 66, [1024] + [1] * 66, [2047],
+                                 [2048, 1], [8200, 600]])
+def test_paged_attn_split_counts(nq, nkv, d, ctx):
+    """The longest batches that are not split (32 pages, 64 with an item per CU), one page more,
+    and split counts on both sides of the merge's 8 (or 16) side-by-side groups."""
+    say(f"case: paged attn split counts nq={nq} nkv={nkv} d={d} ctx={ctx[:2]} x{len(ctx)}")
+    rng = np.random.default_rng(300 + nq + ctx[0])
+    cfg = wl.LayerConfig("t", 256, 256, nq, nkv, d)
+    c = attention_case(cfg, wl.custom_batch(rng, ctx, []), 15, rng)
+    out = torch.empty((len(ctx), nq, d), dtype=torch.uint16, device="cuda")
+    mx.mx_paged_attn(c["mb"], c["shape"], c["q"], c["k"], c["v"], out, c["ws"])
+    sync()
+    assert_rows_close(bits_to_f64(out).reshape(-1, d), c["exp"].reshape(-1, d), what="attention")
+
+
 def test_paged_attn_needle():
     say("case: paged attn needle")
     rng = np.random.default_rng(6)
