@@ -61,17 +61,60 @@ mx_status validate_shape(const mx_attn_shape* s) {
   return MX_OK;
 }
 
+// Whether the new tokens write distinct slots.  A request's new tokens fill runs
+// of consecutive slots of the pages they touch, so a page and the 16-bit mask of
+// the slots written in it stand for up to 16 of them: an open-addressed table of
+// the touched pages, at most half full (sorting the slots instead took most of
+// the host's time of a call that brings a few thousand new tokens).
+bool slots_distinct(const mx_batch* b, int64_t touched) {
+  if (b->num_reqs == 0) return true;
+  int bits = 4;
+  while (((int64_t)1 << bits) < 2 * touched) bits++;
+  struct Entry {
+    int32_t page;    // the page's id + 1 (0: free)
+    uint32_t slots;
+  };
+  std::vector<Entry> table((size_t)1 << bits, Entry{0, 0});
+  const size_t mask = table.size() - 1;
+  for (int r = 0; r < b->num_reqs; r++) {
+    const mx_request& q = b->reqs[r];
+    const int end = q.ctx_len + q.n_new;
+    for (int pos = q.ctx_len; pos < end;) {
+      const int s0 = pos % 16, n = std::min(16 - s0, end - pos);
+      const uint32_t slots = ((1u << n) - 1) << s0;
+      const uint32_t key = (uint32_t)q.pages[pos / 16] + 1u;
+      size_t i = (size_t)((key * 0x9E3779B97F4A7C15ull) >> (64 - bits));
+      while (table[i].page != 0 && table[i].page != (int32_t)key) i = (i + 1) & mask;
+      if (table[i].slots & slots) return false;
+      table[i].page = (int32_t)key;
+      table[i].slots |= slots;
+      pos += n;
+    }
+  }
+  return true;
+}
+
+// The error of a batch whose slots are not distinct: names the lowest one
+// written twice.
+mx_status duplicate_slot(const mx_batch* b, int64_t T) {
+  std::vector<int64_t> slots;
+  slots.reserve((size_t)T);
+  for (int r = 0; r < b->num_reqs; r++)
+    for (int64_t p = b->reqs[r].ctx_len, end = p + b->reqs[r].n_new; p < end; p++)
+      slots.push_back((int64_t)b->reqs[r].pages[p / 16] * 16 + p % 16);
+  std::sort(slots.begin(), slots.end());
+  const auto it = std::adjacent_find(slots.begin(), slots.end());
+  return fail(MX_ERR_INVALID, "two new tokens write the same KV slot %lld",
+              it == slots.end() ? -1ll : (long long)*it);
+}
+
 mx_status validate_batch(const mx_batch* b, const mx_attn_shape* s, int64_t* T_out) {
   if (!b) return fail(MX_ERR_NULL, "batch is NULL");
   mx_status st = validate_shape(s);
   if (st != MX_OK) return st;
   if (b->num_reqs < 0) return fail(MX_ERR_INVALID, "num_reqs %d < 0", b->num_reqs);
   if (b->num_reqs > 0 && !b->reqs) return fail(MX_ERR_NULL, "reqs is NULL");
-  int64_t T = 0;
-  std::vector<int64_t> slots;
-  for (int r = 0; r < b->num_reqs; r++) T += std::max(b->reqs[r].n_new, 0);
-  slots.reserve((size_t)std::min<int64_t>(T, INT32_MAX / 2));
-  T = 0;
+  int64_t T = 0, touched = 0;
   for (int r = 0; r < b->num_reqs; r++) {
     const mx_request& q = b->reqs[r];
     if (q.phase != MX_PREFILL && q.phase != MX_DECODE)
@@ -87,21 +130,20 @@ mx_status validate_batch(const mx_batch* b, const mx_attn_shape* s, int64_t* T_o
       return fail(MX_ERR_NO_SPACE, "request %d: %d pages for %lld tokens (need %lld)", r, q.n_pages,
                   (long long)kv_len, (long long)need);
     if (!q.pages) return fail(MX_ERR_NULL, "request %d: pages is NULL", r);
-    for (int i = 0; i < q.n_pages; i++)
-      if (q.pages[i] < 0 || q.pages[i] >= s->pool_pages)
-        return fail(MX_ERR_INVALID, "request %d: page id %d outside [0, %lld)", r, q.pages[i],
-                    (long long)s->pool_pages);
-    for (int i = 0; i < q.n_new; i++) {
-      const int64_t p = (int64_t)q.ctx_len + i;
-      slots.push_back((int64_t)q.pages[p / 16] * 16 + p % 16);
-    }
+    // one branch-free pass over the ids (a negative one is a large unsigned one)
+    const uint32_t limit = (uint32_t)std::min<int64_t>(s->pool_pages, (int64_t)1 << 31);
+    bool bad = s->pool_pages < 0;
+    for (int i = 0; i < q.n_pages; i++) bad |= (uint32_t)q.pages[i] >= limit;
+    if (bad)
+      for (int i = 0; i < q.n_pages; i++)
+        if (q.pages[i] < 0 || q.pages[i] >= s->pool_pages)
+          return fail(MX_ERR_INVALID, "request %d: page id %d outside [0, %lld)", r, q.pages[i],
+                      (long long)s->pool_pages);
+    touched += (kv_len - 1) / 16 - q.ctx_len / 16 + 1;
     T += q.n_new;
     if (T > INT32_MAX / 2) return fail(MX_ERR_TOO_LARGE, "too many tokens");
   }
-  std::sort(slots.begin(), slots.end());
-  for (size_t i = 1; i < slots.size(); i++)
-    if (slots[i] == slots[i - 1])
-      return fail(MX_ERR_INVALID, "two new tokens write the same KV slot %lld", (long long)slots[i]);
+  if (!slots_distinct(b, touched)) return duplicate_slot(b, T);
   if (T_out) *T_out = T;
   return MX_OK;
 }
@@ -122,13 +164,15 @@ mx_status validate_cfg(const mx_layer_cfg* c) {
 // ------------------------------------------------------------------ planning
 constexpr int kXcds = 8;  // accelerator dies: workgroup b runs on die b % 8
 
+// What a call needs to know of its batch before it lays out the workspace; the
+// metadata itself is written where it goes (pack_meta).
 struct Plan {
+  const mx_batch* batch = nullptr;
   int R = 0, T = 0;
   std::vector<ReqDev> reqs;
-  std::vector<int32_t> pages;
-  std::vector<AttnItem> items;
   std::vector<MergeItem> merges;
-  int64_t n_parts = 0;
+  int64_t n_pages = 0, n_items = 0, n_parts = 0;
+  int64_t n_tiles = 0;       // prefill tiles (work items: one per q head each)
   int split_pages = 16;
   int group = 1;
   bool has_prefill = false;  // some work item is a prefill tile
@@ -170,10 +214,13 @@ int choose_split_pages(const mx_batch* b, const mx_attn_shape* s) {
 }
 
 void build_plan(const mx_batch* b, const mx_attn_shape* s, bool with_items, Plan& p) {
+  p.batch = b;
   p.R = b->num_reqs;
   p.group = s->n_q_heads / s->n_kv_heads;
   p.split_pages = choose_split_pages(b, s);
   p.reqs.resize(p.R);
+  const int nq = s->n_q_heads;
+  const int64_t sub = s->n_kv_heads * ceil_div(p.group, 16);  // decode items per split
   int tok = 0, pg = 0;
   for (int r = 0; r < p.R; r++) {
     const mx_request& q = b->reqs[r];
@@ -188,79 +235,98 @@ void build_plan(const mx_batch* b, const mx_attn_shape* s, bool with_items, Plan
     d.n_split = 1;
     tok += q.n_new;
     pg += d.n_pages;
+    if (!with_items) continue;
+    if (d.phase == MX_PREFILL) {
+      p.n_tiles += ceil_div(d.n_new, kPrefillTileRows);
+    } else {
+      d.n_split = (int)ceil_div(d.n_pages, p.split_pages);
+      if (d.n_split > 1) {
+        p.merges.push_back(MergeItem{r, (int32_t)p.n_parts});
+        p.n_parts += (int64_t)nq * d.n_split;
+      }
+      p.n_items += d.n_split * sub;
+    }
   }
+  p.n_items += p.n_tiles * nq;
+  p.has_prefill = p.n_tiles > 0;
   p.T = tok;
-  p.pages.resize(pg);
-  for (int r = 0; r < p.R; r++)
-    std::copy(b->reqs[r].pages, b->reqs[r].pages + p.reqs[r].n_pages,
-              p.pages.begin() + p.reqs[r].page_start);
-  if (!with_items) return;
+  p.n_pages = pg;
+}
+
+// The attention's work items, p.n_items of them, in launch order.
+void write_items(const Plan& p, const mx_attn_shape* s, AttnItem* out) {
   const int nq = s->n_q_heads;
-  // prefill q tiles (heaviest work first: later tiles see more keys)
+  // The hardware hands workgroups to free slots in list order, so the longest
+  // items must not be left for the end: prefill tiles by the keys their last
+  // rows scan, and the decode splits by page count, each longest first.
+  struct Tile {
+    int req, start, keys;
+  };
+  std::vector<Tile> tiles;
+  tiles.reserve(p.n_tiles);
   for (int r = 0; r < p.R; r++) {
     const ReqDev& d = p.reqs[r];
     if (d.phase != MX_PREFILL) continue;
-    const int tiles = (int)ceil_div(d.n_new, kPrefillTileRows);
-    for (int qt = tiles - 1; qt >= 0; qt--)
-      for (int h = 0; h < nq; h++) {
-        AttnItem it;
-        it.req = r;
-        it.head = (int16_t)h;
-        it.kind = 1;
-        it.nrows = 16;
-        it.start = qt * kPrefillTileRows;
-        it.part = 0;
-        p.items.push_back(it);
-      }
+    for (int t = (d.n_new - 1) / kPrefillTileRows; t >= 0; t--) {
+      const int start = t * kPrefillTileRows;
+      tiles.push_back({r, start, d.ctx_len + std::min(start + kPrefillTileRows, d.n_new)});
+    }
   }
-  // the hardware hands workgroups to free slots in list order, so the longest
-  // items must not be left for the end: prefill tiles by the keys their last
-  // rows scan, and the decode splits by page count, each longest first
-  auto longer = [&](const AttnItem& a, const AttnItem& b) {
-    const ReqDev& ra = p.reqs[a.req];
-    const ReqDev& rb = p.reqs[b.req];
-    return ra.ctx_len + std::min(a.start + kPrefillTileRows, ra.n_new) >
-           rb.ctx_len + std::min(b.start + kPrefillTileRows, rb.n_new);
-  };
+  auto longer = [](const Tile& a, const Tile& b) { return a.keys > b.keys; };
   // (one prompt's tiles are generated in this order already)
-  if (!std::is_sorted(p.items.begin(), p.items.end(), longer))
-    std::stable_sort(p.items.begin(), p.items.end(), longer);
-  // decode splits, longest first: a stable counting sort on the split's page
-  // count (1 .. split_pages), so equal lengths keep request, split and head order
-  std::vector<AttnItem> dec;
-  std::vector<int64_t> count(p.split_pages + 2, 0);
-  for (int r = 0; r < p.R; r++) {
-    ReqDev& d = p.reqs[r];
-    if (d.phase != MX_DECODE) continue;
-    const int ns = (int)ceil_div(d.n_pages, p.split_pages);
-    d.n_split = ns;
-    int64_t part_base = 0;
-    if (ns > 1) {
-      part_base = p.n_parts;
-      p.n_parts += (int64_t)nq * ns;
-      p.merges.push_back(MergeItem{r, (int32_t)part_base});
+  if (!std::is_sorted(tiles.begin(), tiles.end(), longer))
+    std::stable_sort(tiles.begin(), tiles.end(), longer);
+  auto prefill = [&](const Tile& t, int head) {
+    return AttnItem{t.req, (int16_t)head, 1, 16, t.start, 0};
+  };
+  // Decode splits: the whole ones of every request, then the requests' last
+  // parts by a stable counting sort on their page count (1 .. split_pages; a
+  // last part may be whole), so equal lengths keep request, split and head order.
+  const int64_t nD = p.n_items - p.n_tiles * nq;
+  std::vector<AttnItem> dec(p.n_tiles ? nD : 0);
+  AttnItem* dp = p.n_tiles ? dec.data() : out;
+  int64_t part_base = 0;
+  auto split = [&](int r, int sp, int64_t base) {
+    const ReqDev& d = p.reqs[r];
+    for (int g = 0; g < s->n_kv_heads; g++)
+      for (int h0 = 0; h0 < p.group; h0 += 16) {
+        const int head = g * p.group + h0;
+        *dp++ = AttnItem{r, (int16_t)head, 0, (int8_t)std::min(16, p.group - h0),
+                         sp * p.split_pages, (int32_t)(base + (int64_t)head * d.n_split + sp)};
+      }
+  };
+  struct Last {
+    int req;
+    int64_t base;
+  };
+  std::vector<Last> last;
+  std::vector<int> count(p.split_pages + 2, 0);  // by decreasing page count
+  if (nD > 0) {
+    std::vector<std::pair<int, Last>> unsorted;
+    unsorted.reserve(p.R);
+    for (int r = 0; r < p.R; r++) {
+      const ReqDev& d = p.reqs[r];
+      if (d.phase != MX_DECODE) continue;
+      const int64_t base = d.n_split > 1 ? part_base : 0;
+      const int rest = d.n_pages - (d.n_split - 1) * p.split_pages;
+      const int whole = d.n_split - (rest < p.split_pages);
+      for (int sp = 0; sp < whole; sp++) split(r, sp, base);
+      if (rest < p.split_pages) {
+        unsorted.push_back({p.split_pages - rest, Last{r, base}});
+        count[p.split_pages - rest + 1]++;
+      }
+      if (d.n_split > 1) part_base += (int64_t)nq * d.n_split;
     }
-    for (int sp = 0; sp < ns; sp++) {
-      const int len = std::min(p.split_pages, d.n_pages - sp * p.split_pages);
-      for (int g = 0; g < s->n_kv_heads; g++)
-        for (int h0 = 0; h0 < p.group; h0 += 16) {
-          AttnItem it;
-          it.req = r;
-          it.head = (int16_t)(g * p.group + h0);
-          it.kind = 0;
-          it.nrows = (int8_t)std::min(16, p.group - h0);
-          it.start = sp * p.split_pages;
-          it.part = (int32_t)(part_base + (int64_t)it.head * ns + sp);
-          dec.push_back(it);
-          count[p.split_pages - len + 1]++;
-        }
-    }
+    for (size_t i = 1; i < count.size(); i++) count[i] += count[i - 1];
+    last.resize(unsorted.size());
+    for (const auto& u : unsorted) last[count[u.first]++] = u.second;
+    for (const Last& l : last) split(l.req, p.reqs[l.req].n_split - 1, l.base);
   }
-  for (size_t i = 1; i < count.size(); i++) count[i] += count[i - 1];
-  std::vector<AttnItem> dsorted(dec.size());
-  for (const AttnItem& it : dec) {
-    const int len = std::min(p.split_pages, p.reqs[it.req].n_pages - it.start);
-    dsorted[count[p.split_pages - len]++] = it;
+  if (!p.n_tiles) return;
+  if (nD == 0) {
+    for (const Tile& t : tiles)
+      for (int h = 0; h < nq; h++) *out++ = prefill(t, h);
+    return;
   }
   // Prefill tiles (matrix-core bound) and decode splits (bound by HBM) are
   // interleaved in proportion to their counts, each list keeping its own
@@ -275,36 +341,37 @@ void build_plan(const mx_batch* b, const mx_attn_shape* s, bool with_items, Plan
   // values through one L2 instead of all eight, which leaves more of the
   // fabric to the decode stream beside them: the 70B launch at P = 8192 took
   // 2.10 ms against 2.24 ms with one list for all XCDs (same at P <= 4096).
-  p.has_prefill = !p.items.empty();
-  const std::vector<AttnItem> pre(std::move(p.items));
-  const size_t nP = pre.size(), nD = dsorted.size();
-  p.items.clear();
-  p.items.reserve(nP + nD);
-  auto interleave = [](const std::vector<AttnItem>& a, const std::vector<AttnItem>& b,
-                       std::vector<AttnItem>& out) {
-    for (size_t i = 0, j = 0; i < a.size() || j < b.size();) {
-      // the list that is behind in its fraction done goes next
-      if (j >= b.size() || (i < a.size() && (double)i * b.size() <= (double)j * a.size()))
-        out.push_back(a[i++]);
-      else
-        out.push_back(b[j++]);
-    }
-  };
-  if (nP == 0 || nD == 0) {
-    interleave(pre, dsorted, p.items);
-    return;
-  }
-  std::vector<AttnItem> px[kXcds], dx[kXcds], sub[kXcds];
-  for (const AttnItem& it : pre) px[(it.head / p.group) % kXcds].push_back(it);
-  for (size_t j = 0; j < nD; j++) dx[j % kXcds].push_back(dsorted[j]);
-  size_t longest = 0;
+  struct Lane {
+    std::vector<int> heads;        // q heads of this XCD's prefill tiles
+    int64_t n_pre, n_dec;          // items of either kind
+    int64_t i = 0, j = 0;          // next of either
+    size_t tile = 0, head = 0;     // the next prefill item
+  } lane[kXcds];
+  for (int h = 0; h < nq; h++) lane[(h / p.group) % kXcds].heads.push_back(h);
+  int64_t longest = 0;
   for (int x = 0; x < kXcds; x++) {
-    interleave(px[x], dx[x], sub[x]);
-    longest = std::max(longest, sub[x].size());
+    Lane& l = lane[x];
+    l.n_pre = p.n_tiles * (int64_t)l.heads.size();
+    l.n_dec = (nD - x + kXcds - 1) / kXcds;
+    longest = std::max(longest, l.n_pre + l.n_dec);
   }
-  for (size_t j = 0; j < longest; j++)
-    for (int x = 0; x < kXcds; x++)
-      if (j < sub[x].size()) p.items.push_back(sub[x][j]);
+  for (int64_t k = 0; k < longest; k++)
+    for (int x = 0; x < kXcds; x++) {
+      Lane& l = lane[x];
+      if (k >= l.n_pre + l.n_dec) continue;
+      // the list that is behind in its fraction done goes next
+      if (l.j >= l.n_dec ||
+          (l.i < l.n_pre && (double)l.i * (double)l.n_dec <= (double)l.j * (double)l.n_pre)) {
+        *out++ = prefill(tiles[l.tile], l.heads[l.head]);
+        l.i++;
+        if (++l.head == l.heads.size()) {
+          l.head = 0;
+          l.tile++;
+        }
+      } else {
+        *out++ = dec[kXcds * l.j++ + x];
+      }
+    }
 }
 
 // ------------------------------------------------------------------ workspace layout
@@ -362,8 +429,7 @@ Layout make_layout(int64_t R, int64_t T, int64_t n_pages, int64_t n_items, int64
 
 Layout layout_for(const Plan& p, const mx_attn_shape* s, const mx_layer_cfg* c) {
   const size_t sc = c ? gemm_scratch_bound(c, p.T) : 0;
-  return make_layout(p.R, p.T, (int64_t)p.pages.size(), (int64_t)p.items.size(),
-                     (int64_t)p.merges.size(), p.n_parts, s, c, sc);
+  return make_layout(p.R, p.T, p.n_pages, p.n_items, (int64_t)p.merges.size(), p.n_parts, s, c, sc);
 }
 
 // ------------------------------------------------------------------ per-device state
@@ -441,18 +507,33 @@ hipError_t close_group(DeviceState* ds, int last) {
   return hipSuccess;
 }
 
+// Rotary inverse frequencies theta^(-2 k / d), k < d / 2 (the last pair of
+// (theta, d) is kept per thread: the powers cost as much as a launch).
+const double* inv_freqs(float theta, int d) {
+  thread_local float last_theta = 0.f;
+  thread_local int last_d = 0;
+  thread_local double inv[64];
+  if (theta != last_theta || d != last_d) {
+    for (int k = 0; k < d / 2; k++) inv[k] = std::pow((double)theta, -2.0 * k / d);
+    last_theta = theta;
+    last_d = d;
+  }
+  return inv;
+}
+
 // The metadata block [0, L.meta_end) of the workspace, as the kernels read it:
 // request records, page tables, attention work items, merge items, rotary
-// inverse frequencies.
+// inverse frequencies (the gaps between them are never read).
 void pack_meta(const Plan& p, const Layout& L, const mx_attn_shape* s, float theta, char* h) {
-  memset(h, 0, L.meta_end);
   if (!p.reqs.empty()) memcpy(h + L.reqs, p.reqs.data(), p.reqs.size() * sizeof(ReqDev));
-  if (!p.pages.empty()) memcpy(h + L.pages, p.pages.data(), p.pages.size() * sizeof(int32_t));
-  if (!p.items.empty()) memcpy(h + L.items, p.items.data(), p.items.size() * sizeof(AttnItem));
+  int32_t* pages = (int32_t*)(h + L.pages);
+  for (int r = 0; r < p.R; r++)
+    memcpy(pages + p.reqs[r].page_start, p.batch->reqs[r].pages,
+           (size_t)p.reqs[r].n_pages * sizeof(int32_t));
+  if (p.n_items) write_items(p, s, (AttnItem*)(h + L.items));
   if (!p.merges.empty()) memcpy(h + L.merges, p.merges.data(), p.merges.size() * sizeof(MergeItem));
-  double* inv = (double*)(h + L.inv_freq);
   const int d = s->head_dim;
-  for (int k = 0; k < d / 2; k++) inv[k] = std::pow((double)theta, -2.0 * k / d);
+  memcpy(h + L.inv_freq, inv_freqs(theta, d), (d / 2) * sizeof(double));
 }
 
 // Runs pack(host) on a staging buffer of at least `bytes` and launch(device
@@ -804,7 +885,7 @@ MX_EXPORT mx_status mx_paged_attn(const mx_batch* batch, const mx_attn_shape* sh
   AttnParams a = attn_params(p, L, shape, ws, q, (int64_t)shape->n_q_heads * shape->head_dim,
                              k_pool, v_pool, out);
   hipError_t e = timed("paged_attn", stream, [&] {
-    return launch_paged_attn(a, (int)p.items.size(), at<MergeItem>(ws, L.merges),
+    return launch_paged_attn(a, (int)p.n_items, at<MergeItem>(ws, L.merges),
                              (int)p.merges.size(), shape->head_dim, stream);
   });
   if (e != hipSuccess) return hip_fail(e, "attention launch");
@@ -889,7 +970,7 @@ MX_EXPORT mx_status mx_paged_attn_static(const mx_batch* batch, const mx_attn_sh
   AttnParams a = attn_params(p, L, shape, ws, q, (int64_t)shape->n_q_heads * shape->head_dim,
                              k_pool, v_pool, out);
   e = timed("paged_attn", stream, [&] {
-    return launch_paged_attn(a, (int)p.items.size(), at<MergeItem>(ws, L.merges),
+    return launch_paged_attn(a, (int)p.n_items, at<MergeItem>(ws, L.merges),
                              (int)p.merges.size(), shape->head_dim, stream);
   });
   if (e != hipSuccess) return hip_fail(e, "attention launch");
@@ -954,7 +1035,7 @@ MX_EXPORT mx_status mx_layer_step(const mx_batch* batch, const mx_layer_cfg* cfg
     AttnParams a = attn_params(p, L, s, ws, q, (int64_t)nq * d, k_pool, v_pool, o);
     a.out_tiled = 1;  // o feeds the output projection
     MX_CK(timed("paged_attn", stream, [&] {
-            return launch_paged_attn(a, (int)p.items.size(), at<MergeItem>(ws, L.merges),
+            return launch_paged_attn(a, (int)p.n_items, at<MergeItem>(ws, L.merges),
                                      (int)p.merges.size(), d, stream);
           }), "attention launch")
   }

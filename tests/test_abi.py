@@ -66,6 +66,33 @@ def test_validation_errors(batch, status):
     assert mx.last_error() != ""
 
 
+@pytest.mark.parametrize("seed", range(4))
+def test_distinct_slots_against_brute_force(seed):
+    """Random batches over few pages, whose requests share pages in every way (disjoint slots of
+    one page, a page twice in a table, overlaps): refused exactly when two new tokens write one
+    slot, naming the lowest such slot."""
+    rng = np.random.default_rng(seed)
+    refused = 0
+    for _ in range(150):
+        pool = int(rng.choice([4, 12, 2000]))
+        phase, n_new, ctx, tables, slots = [], [], [], [], []
+        for _ in range(rng.integers(1, 7)):
+            dec = rng.random() < 0.4
+            n_new.append(1 if dec else int(rng.integers(1, 40)))
+            ctx.append(int(rng.integers(1 if dec else 0, 40)))
+            phase.append(mx.MX_DECODE if dec else mx.MX_PREFILL)
+            t = rng.integers(0, pool, -(-(n_new[-1] + ctx[-1]) // 16))
+            tables.append(t)
+            slots += [int(t[p // 16]) * 16 + p % 16 for p in range(ctx[-1], ctx[-1] + n_new[-1])]
+        st = mx.mx_batch_validate(mx.Batch(phase, n_new, ctx, tables), shape64(pool))
+        twice = sorted(s for s in set(slots) if slots.count(s) > 1)
+        assert st == (mx.MX_ERR_INVALID if twice else mx.MX_OK)
+        if twice:
+            refused += 1
+            assert mx.last_error().endswith(f"the same KV slot {twice[0]}")
+    assert 0 < refused < 150
+
+
 def test_validation_accepts_shared_prefix_and_boundaries():
     # two decodes reading the same (shared, read-only) first page, writing distinct slots
     b = mx.Batch([1, 1, 0], [1, 1, 16], [16, 17, 0], [[2, 3], [2, 4], [9]])
