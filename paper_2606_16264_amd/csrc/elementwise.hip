@@ -1,5 +1,5 @@
 // elementwise.hip -- the memory-bound kernels of the layer step on gfx950:
-// token map + rotary table, RMSNorm, KV append, gather, weight packing.
+// metadata upload + rotary table, RMSNorm, KV append, gather, weight packing.
 #include <algorithm>
 
 #include "mx_device.h"
@@ -9,65 +9,37 @@ namespace mx {
 
 namespace {
 
-// ---------------------------------------------------------------- token map
-// One thread per (token, rotary pair).  The token's request is found by binary
-// search over the requests' first rows (copied to LDS first when they fit, so
-// that the search does not chain global-memory round trips); token
-// t = tok_start + i of request r sits at position ctx_len + i and writes slot
-// page * 16 + pos % 16.  The rotary angle pos * theta^(-2i/d) is formed and
-// reduced modulo 2 pi in double precision; its cosine and sine are then taken
-// in single precision.
-constexpr int kLdsReqs = 4096;
-
-struct TokenMapArgs {
-  const ReqDev* reqs;
-  int R, T;
-  const int32_t* pages;
-  int32_t* tok_req;
-  int32_t* tok_pos;
-  int64_t* tok_slot;
-  const double* inv_freq;
-  float2* rope_cs;
-  int half;
-};
+// ---------------------------------------------------------------- rotary table
+// The (cos, sin) table of the batch's tokens, kRopeTokens tokens per block: the
+// rotary angle pos * theta^(-2i/d) is formed and reduced modulo 2 pi in double
+// precision; its cosine and sine are then taken in single precision.  The
+// positions may lie in pinned host memory: a block reads 64 bytes of them.
+constexpr int kRopeTokens = 16;
 
 // Block-uniform: every thread of the block calls it (it synchronises the block).
-__device__ __forceinline__ void token_map_block(const TokenMapArgs& a, int block, int* s_start) {
-  const bool in_lds = a.R <= kLdsReqs;
-  if (in_lds) {
-    for (int r = threadIdx.x; r < a.R; r += blockDim.x) s_start[r] = a.reqs[r].tok_start;
-    __syncthreads();
-  }
-  const int64_t idx = (int64_t)block * blockDim.x + threadIdx.x;
-  const int t = (int)(idx / a.half), i = (int)(idx % a.half);
-  if (t >= a.T) return;
-  int lo = 0, hi = a.R - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    const int start = in_lds ? s_start[mid] : a.reqs[mid].tok_start;
-    if (start <= t) lo = mid; else hi = mid - 1;
-  }
-  const ReqDev rq = a.reqs[lo];
-  const int pos = rq.ctx_len + (t - rq.tok_start);
-  if (i == 0) {
-    const int64_t page = a.pages[rq.page_start + pos / 16];
-    a.tok_req[t] = lo;
-    a.tok_pos[t] = pos;
-    a.tok_slot[t] = page * 16 + pos % 16;
-  }
-  if (a.rope_cs) {
-    const double ang = (double)pos * a.inv_freq[i];
+__device__ __forceinline__ void rope_block(const int32_t* __restrict__ tok_pos, int T,
+                                           const RopeFreqs& freqs, float2* __restrict__ rope_cs,
+                                           int half, int block, int* s_pos) {
+  const int t0 = block * kRopeTokens, n = min(kRopeTokens, T - t0);
+  if ((int)threadIdx.x < n) s_pos[threadIdx.x] = tok_pos[t0 + threadIdx.x];
+  __syncthreads();
+  const int i = threadIdx.x % half;  // half is 32 or 64
+  const double f = freqs.inv[i];
+  for (int k = threadIdx.x / half; k < n; k += blockDim.x / half) {
+    const double ang = (double)s_pos[k] * f;
     const double two_pi = 6.283185307179586476925286766559;
     const double r = ang - rint(ang / two_pi) * two_pi;
     float sn, cs;
     sincosf((float)r, &sn, &cs);
-    a.rope_cs[(int64_t)t * a.half + i] = make_float2(cs, sn);
+    rope_cs[(int64_t)(t0 + k) * half + i] = make_float2(cs, sn);
   }
 }
 
-__global__ __launch_bounds__(256) void token_map_kernel(TokenMapArgs a) {
-  __shared__ int s_start[kLdsReqs];
-  token_map_block(a, blockIdx.x, s_start);
+// 16-byte words first, first + step, ... of n from src (pinned host memory, read
+// through its device mapping) to dst.
+__device__ __forceinline__ void copy_words(const u32x4* __restrict__ src, u32x4* __restrict__ dst,
+                                           int64_t n, int64_t first, int64_t step) {
+  for (int64_t i = first; i < n; i += step) dst[i] = src[i];
 }
 
 // ---------------------------------------------------------------- RMSNorm
@@ -258,20 +230,37 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const uint16_t* __restrict
   rmsnorm_pair(x, g, out, H, eps, blockIdx.x, T, red);
 }
 
-// The first kernel of a layer step: the token map (blocks 0 .. map_blocks - 1)
-// and the first RMSNorm (one block per pair of rows after them), which do not
-// depend on each other, in one launch.
-__global__ __launch_bounds__(256) void prologue_kernel(TokenMapArgs a, int map_blocks,
+// The first kernel of a layer step: the metadata upload (blocks 0 .. copy_blocks
+// - 1, first because the host link is the slowest), the rotary table and the
+// first RMSNorm (one block per pair of rows), which do not depend on each other:
+// the table's positions are read from the staging buffer itself.  As launches of
+// their own the upload and the rest took 3.0 + 3.4 us on a tiny layer and 5.2 +
+// 4.9 us on the 7B decode batch, and the host a launch more.
+__global__ __launch_bounds__(256) void prologue_kernel(const u32x4* __restrict__ src,
+                                                       u32x4* __restrict__ dst, int64_t words,
+                                                       int copy_blocks,
+                                                       const int32_t* __restrict__ tok_pos,
+                                                       RopeFreqs freqs, float2* __restrict__ rope_cs,
+                                                       int half, int T,
                                                        const uint16_t* __restrict__ x,
                                                        const uint16_t* __restrict__ g,
                                                        uint16_t* __restrict__ out, int H,
                                                        float eps) {
-  __shared__ int s_start[kLdsReqs];
-  if ((int)blockIdx.x < map_blocks)
-    token_map_block(a, blockIdx.x, s_start);
+  __shared__ int s_mem[kRopeTokens];
+  static_assert(kRopeTokens >= 8, "the norm's eight partial sums");
+  int block = blockIdx.x;
+  if (block < copy_blocks) {
+    copy_words(src, dst, words, (int64_t)block * blockDim.x + threadIdx.x,
+               (int64_t)copy_blocks * blockDim.x);
+    return;
+  }
+  block -= copy_blocks;
+  const int rope_blocks = (T + kRopeTokens - 1) / kRopeTokens;
+  if (block < rope_blocks)
+    rope_block(tok_pos, T, freqs, rope_cs, half, block, s_mem);
   else
-    rmsnorm_pair(x, g, out, H, eps, (int64_t)blockIdx.x - map_blocks, a.T,
-                 reinterpret_cast<float*>(s_start));
+    rmsnorm_pair(x, g, out, H, eps, (int64_t)block - rope_blocks, T,
+                 reinterpret_cast<float*>(s_mem));
 }
 
 // ---------------------------------------------------------------- KV append
@@ -397,14 +386,14 @@ __global__ __launch_bounds__(256) void pack_tiled_kernel(const uint16_t* __restr
   }
 }
 
-// Metadata upload: 16-byte words from the pinned host staging buffer (read
-// through its device mapping) into the workspace.
+// Metadata upload of the entry points without a prologue.
 __global__ __launch_bounds__(256) void upload_kernel(const u32x4* __restrict__ src,
                                                      u32x4* __restrict__ dst, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    dst[i] = src[i];
+  copy_words(src, dst, n, (int64_t)blockIdx.x * blockDim.x + threadIdx.x,
+             (int64_t)gridDim.x * blockDim.x);
 }
+
+int copy_blocks_for(int64_t words) { return (int)std::min<int64_t>((words + 255) / 256, 1024); }
 
 }  // namespace
 
@@ -413,34 +402,25 @@ hipError_t launch_upload(const void* host_mapped, void* dst, size_t bytes, hipSt
   if (bytes % 16 != 0 || (size_t)host_mapped % 16 != 0 || (size_t)dst % 16 != 0)
     return hipErrorInvalidValue;
   const int64_t n = (int64_t)(bytes / 16);
-  const int blocks = (int)std::min<int64_t>((n + 255) / 256, 1024);
+  const int blocks = copy_blocks_for(n);
   upload_kernel<<<blocks, 256, 0, stream>>>(static_cast<const u32x4*>(host_mapped),
                                             static_cast<u32x4*>(dst), n);
   return hipGetLastError();
 }
 
-hipError_t launch_token_map(const ReqDev* reqs, int R, int T, const int32_t* pages,
-                            int32_t* tok_req, int32_t* tok_pos, int64_t* tok_slot,
-                            const double* inv_freq, float2* rope_cs, int half,
-                            hipStream_t stream) {
-  if (R == 0 || T == 0) return hipSuccess;
-  if (!rope_cs) half = 1;
-  const int64_t n = (int64_t)T * half;
-  const TokenMapArgs a{reqs, R, T, pages, tok_req, tok_pos, tok_slot, inv_freq, rope_cs, half};
-  token_map_kernel<<<(unsigned)((n + 255) / 256), 256, 0, stream>>>(a);
-  return hipGetLastError();
-}
-
-hipError_t launch_prologue(const ReqDev* reqs, int R, int T, const int32_t* pages,
-                           int32_t* tok_req, int32_t* tok_pos, int64_t* tok_slot,
-                           const double* inv_freq, float2* rope_cs, int half,
-                           const uint16_t* x, const uint16_t* g, uint16_t* out, int H, float eps,
-                           hipStream_t stream) {
-  if (R == 0 || T == 0) return hipSuccess;
-  const int64_t map_blocks = ((int64_t)T * half + 255) / 256;
-  const TokenMapArgs a{reqs, R, T, pages, tok_req, tok_pos, tok_slot, inv_freq, rope_cs, half};
-  prologue_kernel<<<(unsigned)(map_blocks + (T + 1) / 2), 256, 0, stream>>>(a, (int)map_blocks, x,
-                                                                            g, out, H, eps);
+hipError_t launch_prologue(const void* host_mapped, void* dst, size_t bytes,
+                           const int32_t* tok_pos, int T, const RopeFreqs& freqs, float2* rope_cs,
+                           int half, const uint16_t* x, const uint16_t* g, uint16_t* out, int H,
+                           float eps, hipStream_t stream) {
+  if (T == 0) return hipSuccess;
+  if (bytes % 16 != 0 || (size_t)host_mapped % 16 != 0 || (size_t)dst % 16 != 0)
+    return hipErrorInvalidValue;
+  const int64_t words = (int64_t)(bytes / 16);
+  const int copy_blocks = copy_blocks_for(words);
+  const int rope_blocks = (T + kRopeTokens - 1) / kRopeTokens;
+  prologue_kernel<<<copy_blocks + rope_blocks + (T + 1) / 2, 256, 0, stream>>>(
+      static_cast<const u32x4*>(host_mapped), static_cast<u32x4*>(dst), words, copy_blocks,
+      tok_pos, freqs, rope_cs, half, T, x, g, out, H, eps);
   return hipGetLastError();
 }
 

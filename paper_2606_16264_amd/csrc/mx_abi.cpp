@@ -376,8 +376,8 @@ void write_items(const Plan& p, const mx_attn_shape* s, AttnItem* out) {
 
 // ------------------------------------------------------------------ workspace layout
 struct Layout {
-  size_t reqs = 0, pages = 0, items = 0, merges = 0, inv_freq = 0, meta_end = 0;
-  size_t tok_req = 0, tok_pos = 0, tok_slot = 0, rope_cs = 0;
+  size_t reqs = 0, pages = 0, items = 0, merges = 0, meta_end = 0;
+  size_t tok_req = 0, tok_pos = 0, tok_slot = 0, map_end = 0, rope_cs = 0;
   size_t part_o = 0, part_ml = 0;
   size_t h = 0, q = 0, o = 0, x1 = 0, a = 0, scratch = 0, scratch_floats = 0;
   size_t total = 0;
@@ -404,11 +404,11 @@ Layout make_layout(int64_t R, int64_t T, int64_t n_pages, int64_t n_items, int64
   L.pages = o; o = align_up(o + n_pages * sizeof(int32_t));
   L.items = o; o = align_up(o + n_items * sizeof(AttnItem));
   L.merges = o; o = align_up(o + n_merges * sizeof(MergeItem));
-  L.inv_freq = o; o = align_up(o + (d / 2) * sizeof(double));
   L.meta_end = o;
   L.tok_req = o; o = align_up(o + T * 4);
   L.tok_pos = o; o = align_up(o + T * 4);
   L.tok_slot = o; o = align_up(o + T * 8);
+  L.map_end = o;
   L.part_o = o; o = align_up(o + n_parts * d * 4);
   L.part_ml = o; o = align_up(o + n_parts * 8);
   if (c) {
@@ -509,22 +509,38 @@ hipError_t close_group(DeviceState* ds, int last) {
 
 // Rotary inverse frequencies theta^(-2 k / d), k < d / 2 (the last pair of
 // (theta, d) is kept per thread: the powers cost as much as a launch).
-const double* inv_freqs(float theta, int d) {
+const RopeFreqs& rope_freqs(float theta, int d) {
   thread_local float last_theta = 0.f;
   thread_local int last_d = 0;
-  thread_local double inv[64];
+  thread_local RopeFreqs f;
   if (theta != last_theta || d != last_d) {
-    for (int k = 0; k < d / 2; k++) inv[k] = std::pow((double)theta, -2.0 * k / d);
+    for (int k = 0; k < d / 2; k++) f.inv[k] = std::pow((double)theta, -2.0 * k / d);
     last_theta = theta;
     last_d = d;
   }
-  return inv;
+  return f;
+}
+
+// The token map of the batch: request, position and KV slot of every new token.
+void pack_token_map(const Plan& p, const Layout& L, char* h) {
+  int32_t* req = (int32_t*)(h + L.tok_req);
+  int32_t* pos = (int32_t*)(h + L.tok_pos);
+  int64_t* slot = (int64_t*)(h + L.tok_slot);
+  for (int r = 0; r < p.R; r++) {
+    const mx_request& q = p.batch->reqs[r];
+    const int end = q.ctx_len + q.n_new;
+    for (int i = q.ctx_len; i < end; i++) {
+      *req++ = r;
+      *pos++ = i;
+      *slot++ = (int64_t)q.pages[i / 16] * 16 + i % 16;
+    }
+  }
 }
 
 // The metadata block [0, L.meta_end) of the workspace, as the kernels read it:
-// request records, page tables, attention work items, merge items, rotary
-// inverse frequencies (the gaps between them are never read).
-void pack_meta(const Plan& p, const Layout& L, const mx_attn_shape* s, float theta, char* h) {
+// request records, page tables, attention work items, merge items (the gaps
+// between them are never read).
+void pack_meta(const Plan& p, const Layout& L, const mx_attn_shape* s, char* h) {
   if (!p.reqs.empty()) memcpy(h + L.reqs, p.reqs.data(), p.reqs.size() * sizeof(ReqDev));
   int32_t* pages = (int32_t*)(h + L.pages);
   for (int r = 0; r < p.R; r++)
@@ -532,8 +548,6 @@ void pack_meta(const Plan& p, const Layout& L, const mx_attn_shape* s, float the
            (size_t)p.reqs[r].n_pages * sizeof(int32_t));
   if (p.n_items) write_items(p, s, (AttnItem*)(h + L.items));
   if (!p.merges.empty()) memcpy(h + L.merges, p.merges.data(), p.merges.size() * sizeof(MergeItem));
-  const int d = s->head_dim;
-  memcpy(h + L.inv_freq, inv_freqs(theta, d), (d / 2) * sizeof(double));
 }
 
 // Runs pack(host) on a staging buffer of at least `bytes` and launch(device
@@ -591,10 +605,10 @@ mx_status staged(size_t bytes, hipStream_t stream, Pack&& pack, Launch&& launch)
   return MX_OK;
 }
 
-mx_status upload_meta(const Plan& p, const Layout& L, const mx_attn_shape* s, float theta,
-                      void* ws, hipStream_t stream) {
+mx_status upload_meta(const Plan& p, const Layout& L, const mx_attn_shape* s, void* ws,
+                      hipStream_t stream) {
   return staged(
-      L.meta_end, stream, [&](char* h) { pack_meta(p, L, s, theta, h); },
+      L.meta_end, stream, [&](char* h) { pack_meta(p, L, s, h); },
       [&](const void* dev) { return launch_upload(dev, ws, L.meta_end, stream); });
 }
 
@@ -881,7 +895,7 @@ MX_EXPORT mx_status mx_paged_attn(const mx_batch* batch, const mx_attn_shape* sh
   build_plan(batch, shape, true, p);
   const Layout L = layout_for(p, shape, nullptr);
   if ((st = check_ws(L, ws, ws_bytes)) != MX_OK) return st;
-  if ((st = upload_meta(p, L, shape, 1e4f, ws, stream)) != MX_OK) return st;
+  if ((st = upload_meta(p, L, shape, ws, stream)) != MX_OK) return st;
   AttnParams a = attn_params(p, L, shape, ws, q, (int64_t)shape->n_q_heads * shape->head_dim,
                              k_pool, v_pool, out);
   hipError_t e = timed("paged_attn", stream, [&] {
@@ -963,7 +977,7 @@ MX_EXPORT mx_status mx_paged_attn_static(const mx_batch* batch, const mx_attn_sh
   hipError_t e;
   {
     std::lock_guard<std::mutex> g(g_static_host_mu);
-    pack_meta(p, L, shape, 1e4f, g_static_host);  // L.meta_end <= L.total, checked above
+    pack_meta(p, L, shape, g_static_host);  // L.meta_end <= L.total, checked above
     e = hipMemcpyAsync(ws, g_static_host, L.meta_end, hipMemcpyHostToDevice, stream);
   }
   if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync (metadata)");
@@ -996,7 +1010,6 @@ MX_EXPORT mx_status mx_layer_step(const mx_batch* batch, const mx_layer_cfg* cfg
   build_plan(batch, s, true, p);
   const Layout L = layout_for(p, s, cfg);
   if ((st = check_ws(L, ws, ws_bytes)) != MX_OK) return st;
-  if ((st = upload_meta(p, L, s, cfg->rope_theta, ws, stream)) != MX_OK) return st;
   const WLayout W = wlayout(cfg);
   const char* P = (const char*)packed_weights;
   const int H = cfg->hidden, F = cfg->ffn, nq = s->n_q_heads, nkv = s->n_kv_heads,
@@ -1013,14 +1026,22 @@ MX_EXPORT mx_status mx_layer_step(const mx_batch* batch, const mx_layer_cfg* cfg
   hipError_t e;
 #define MX_CK(call, what) \
   if ((e = (call)) != hipSuccess) return hip_fail(e, what);
-  // a1 + a2: token map and rotary table, and RMSNorm 1, in one launch
-  MX_CK(timed("token_map+rmsnorm_1", stream, [&] {
-          return launch_prologue(at<ReqDev>(ws, L.reqs), p.R, p.T, at<int32_t>(ws, L.pages),
-                                 at<int32_t>(ws, L.tok_req), at<int32_t>(ws, L.tok_pos),
-                                 at<int64_t>(ws, L.tok_slot), at<double>(ws, L.inv_freq),
-                                 rope_cs, d / 2, x, (const uint16_t*)(P + W.g1), h, H,
-                                 cfg->rms_eps, stream);
-        }), "prologue launch")
+  // a0-a2: metadata upload (the token map in it), rotary table and RMSNorm 1, in
+  // one launch
+  st = staged(
+      L.map_end, stream,
+      [&](char* b) {
+        pack_meta(p, L, s, b);
+        pack_token_map(p, L, b);
+      },
+      [&](const void* dev) {
+        return timed("token_map+rmsnorm_1", stream, [&] {
+          return launch_prologue(dev, ws, L.map_end, (const int32_t*)((const char*)dev + L.tok_pos),
+                                 p.T, rope_freqs(cfg->rope_theta, d), rope_cs, d / 2, x,
+                                 (const uint16_t*)(P + W.g1), h, H, cfg->rms_eps, stream);
+        });
+      });
+  if (st != MX_OK) return st;
   // a3-a5: QKV projection with RoPE and the KV append fused into its epilogue
   {
     GemmArgs g{h, (const uint16_t*)(P + W.qkv), nullptr, nullptr, scratch, M, Nqkv, H, H, H, 0, 0, EPI_QKV,
@@ -1112,11 +1133,15 @@ MX_EXPORT mx_status mx_debug_token_map(const mx_batch* batch, const mx_attn_shap
   build_plan(batch, shape, false, p);
   const Layout L = layout_for(p, shape, nullptr);
   if ((st = check_ws(L, ws, ws_bytes)) != MX_OK) return st;
-  if ((st = upload_meta(p, L, shape, 1e4f, ws, stream)) != MX_OK) return st;
-  hipError_t e = launch_token_map(at<ReqDev>(ws, L.reqs), p.R, p.T, at<int32_t>(ws, L.pages),
-                                  at<int32_t>(ws, L.tok_req), at<int32_t>(ws, L.tok_pos),
-                                  at<int64_t>(ws, L.tok_slot), nullptr, nullptr, 0, stream);
-  if (e != hipSuccess) return hip_fail(e, "token map launch");
+  st = staged(
+      L.map_end, stream,
+      [&](char* h) {
+        pack_meta(p, L, shape, h);
+        pack_token_map(p, L, h);
+      },
+      [&](const void* dev) { return launch_upload(dev, ws, L.map_end, stream); });
+  if (st != MX_OK) return st;
+  hipError_t e;
   e = hipMemcpyAsync(tok_req, at<int32_t>(ws, L.tok_req), T * 4, hipMemcpyDeviceToDevice, stream);
   if (e == hipSuccess)
     e = hipMemcpyAsync(tok_pos, at<int32_t>(ws, L.tok_pos), T * 4, hipMemcpyDeviceToDevice, stream);
@@ -1139,7 +1164,7 @@ MX_EXPORT mx_status mx_debug_gather(const mx_batch* batch, const mx_attn_shape* 
   build_plan(batch, shape, false, p);
   const Layout L = layout_for(p, shape, nullptr);
   if ((st = check_ws(L, ws, ws_bytes)) != MX_OK) return st;
-  if ((st = upload_meta(p, L, shape, 1e4f, ws, stream)) != MX_OK) return st;
+  if ((st = upload_meta(p, L, shape, ws, stream)) != MX_OK) return st;
   const ReqDev& rq = p.reqs[req];
   hipError_t e = launch_gather(k_pool, v_pool, at<int32_t>(ws, L.pages) + rq.page_start, rq.kv_len,
                                shape->n_kv_heads, shape->head_dim, k_out, v_out, stream);

@@ -35,21 +35,20 @@ hipError_t launch_paged_attn(const AttnParams& p, int n_items, const MergeItem* 
 // of the step does not wait on a cross-engine signal.
 hipError_t launch_upload(const void* host_mapped, void* dst, size_t bytes, hipStream_t stream);
 
-// Plan kernel: tok_req/tok_pos/tok_slot of every new token from the request
-// table and, when rope_cs is given, the RoPE (cos, sin) table [T][d/2] of the
-// tokens' positions (angle formed and reduced in double precision).
-hipError_t launch_token_map(const ReqDev* reqs, int R, int T, const int32_t* pages,
-                            int32_t* tok_req, int32_t* tok_pos, int64_t* tok_slot,
-                            const double* inv_freq, float2* rope_cs, int half,
-                            hipStream_t stream);
+// Rotary inverse frequencies theta^(-2 i / d) of the pairs i < d / 2 (d <= 128).
+struct RopeFreqs {
+  double inv[64];
+};
 
-// The token map with its rotary table and the first RMSNorm (below) in one
-// launch: the first kernel of a layer step.
-hipError_t launch_prologue(const ReqDev* reqs, int R, int T, const int32_t* pages,
-                           int32_t* tok_req, int32_t* tok_pos, int64_t* tok_slot,
-                           const double* inv_freq, float2* rope_cs, int half,
-                           const uint16_t* x, const uint16_t* g, uint16_t* out, int H, float eps,
-                           hipStream_t stream);
+// The first kernel of a layer step, three independent pieces of work in one
+// launch: the metadata upload (as launch_upload), the RoPE (cos, sin) table
+// [T][half] of the tokens' positions (angle formed and reduced in double
+// precision; tok_pos may lie in the staging buffer, seen from the device) and
+// the first RMSNorm (below).
+hipError_t launch_prologue(const void* host_mapped, void* dst, size_t bytes,
+                           const int32_t* tok_pos, int T, const RopeFreqs& freqs, float2* rope_cs,
+                           int half, const uint16_t* x, const uint16_t* g, uint16_t* out, int H,
+                           float eps, hipStream_t stream);
 
 // RMSNorm: out[t] = x[t] / sqrt(mean(x[t]^2) + eps) * g, bf16 in/out, fp32 math.
 // x is row-major [T][H]; out, a projection's input, is in the tile layout
