@@ -82,14 +82,6 @@ __device__ __forceinline__ void tile_coords(int bid, int tiles_m, int tiles_n, i
   tn = in_group / gm;
 }
 
-// silu(g) = g / (1 + e^-g), the quotient through the reciprocal instruction
-// (1 ulp) rather than the IEEE division sequence (about ten instructions per
-// element in the epilogue): the result is rounded to bf16 anyway.  g -> -inf:
-// 1 / inf = 0, so silu -> -0; g -> +inf: g.
-__device__ __forceinline__ float silu(float g) {
-  return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g));
-}
-
 // Fused QKV epilogue for one rotary pair: packed columns c and c + 32 (c in the
 // low 32-column block of a 64-column group) of token row t, fp32 values lo,
 // hi, with the token's KV slot and the pair's (cos, sin) already read.  q and k
@@ -1055,9 +1047,21 @@ hipError_t launch_plan(const GemmArgs& a, const Plan& p, bool reduce, hipStream_
 }
 }  // namespace
 
+namespace {
+// Few rows in the layer's layouts stream the weights (gemm_stream.hip, with both
+// sides measured).  Whole 64-column groups keep the paired epilogues' strips
+// inside N; strips are addressed with 32-bit byte offsets.
+bool streams(const GemmArgs& a) {
+  const bool paired = a.epilogue == EPI_SWIGLU || a.epilogue == EPI_QKV;
+  return a.M <= kStreamMaxM && a.a_tiled && a.b_row == 32 && a.N % (paired ? 64 : 16) == 0 &&
+         a.K <= (1 << 24);
+}
+}  // namespace
+
 hipError_t launch_gemm_config(const GemmArgs& a, size_t ws_floats, int cfg, int ksplit,
                               hipStream_t stream) {
   if (a.M == 0) return hipSuccess;
+  if (cfg < 0 && streams(a)) return launch_gemm_stream(a, stream);
   Plan p = plan_gemm(a.M, a.N, a.K);
   if (cfg >= 0 && cfg < kNumShapes) {
     p = Plan{cfg, ksplit >= 1 ? ksplit : 1, a.M, -1, 0};
@@ -1083,6 +1087,7 @@ hipError_t launch_gemm_unreduced(const GemmArgs& a, size_t ws_floats, int* split
   *split_row = a.M;
   *ksplit = 1;
   if (a.M == 0) return hipSuccess;
+  if (streams(a)) return launch_gemm_stream(a, stream);
   const Plan p = fit_scratch(plan_gemm(a.M, a.N, a.K), a.M, a.N, ws_floats);
   const int ks = p.m_main < a.M ? p.tail_ksplit : p.ksplit;
   if (ks > 1) {

@@ -54,6 +54,14 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, mx_bf16x2));
 }
 
+// silu(g) = g / (1 + e^-g), the quotient through the reciprocal instruction
+// (1 ulp) rather than the IEEE division sequence (about ten instructions per
+// element in the epilogue): the result is rounded to bf16 anyway.  g -> -inf:
+// 1 / inf = 0, so silu -> -0; g -> +inf: g.
+__device__ __forceinline__ float silu(float g) {
+  return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g));
+}
+
 // 16x16x32 bf16 matrix-core product, fp32 accumulate.
 // A: lane l holds row (l % 16), k = 8 * (l / 16) .. +7
 // B: lane l holds col (l % 16), k = 8 * (l / 16) .. +7

@@ -140,6 +140,11 @@ inline void set_b_tiled(GemmArgs& g) {
   g.b_kstep = 512;
 }
 
+// The GEMM of a few rows (M <= kStreamMaxM, A and B in their tile layouts, N % 16
+// == 0, N % 64 == 0 for the SwiGLU and QKV epilogues): streams the weights.
+constexpr int kStreamMaxM = 16;
+hipError_t launch_gemm_stream(const GemmArgs& args, hipStream_t stream);
+
 // Chooses a tile shape and split for the problem; ws_floats is the fp32
 // scratch available at args.partial.  A K split never needs more than
 // kMaxSplitFloats of scratch (256 MB: enough for a three-way split of the

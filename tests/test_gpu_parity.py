@@ -388,6 +388,15 @@ def test_gemm_tiled_weights(tile_cfg, M, N, K, epi, ksplit):
     gemm_case(M, N, K, epi, tile_cfg=tile_cfg, ksplit=ksplit, b_tiled=True)
 
 
+# The streaming kernel of up to 16 rows (and the first row count past it): fewer K steps than
+# its waves, a K that is no whole number of its rings, odd strip and group counts
+@pytest.mark.parametrize("M", [1, 7, 16, 17])
+@pytest.mark.parametrize("N,K,epi", [(48, 64, 0), (112, 1088, 1), (192, 64, 2), (320, 1152, 2),
+                                     (16, 4160, 0), (4160, 512, 1)])
+def test_gemm_few_rows(M, N, K, epi):
+    gemm_case(M, N, K, epi, b_tiled=True)
+
+
 # N not a multiple of 4: the element-wise split-K reduce (plain and residual)
 @pytest.mark.parametrize("tile_cfg", [0, 3])
 @pytest.mark.parametrize("M,N,K,epi,ksplit", [(131, 1090, 512, 1, 2), (70, 775, 1024, 0, 4)])
@@ -760,6 +769,25 @@ def test_layer_step_degenerate_batches(case):
     written = set(oracle.token_map(b.n_new, b.ctx_len, b.page_tables, 16).tok_slot.tolist())
     assert changed_slots(got["k0"], got["k"], False) <= written
     assert changed_slots(got["v0"], got["v"], True) <= written
+
+
+@pytest.mark.parametrize("dec,pre", [([70, 5], [(9, 3)]), ([15, 16, 300], [(13, 0)])])
+def test_layer_step_few_rows_head_dim_64(dec, pre):
+    """Up to 16 rows of a head_dim 64 layer (the streaming projections' other rotary layout)."""
+    say(f"case: layer step few rows, head_dim 64, {dec} {pre}")
+    cfg = wl.CONFIGS["c1"]
+    rng = np.random.default_rng(len(dec))
+    b = wl.custom_batch(rng, dec, pre)
+    assert b.T <= 16
+    w = small_weights(rng, cfg)
+    x = wl.f32_to_bf16_bits(rng.standard_normal((b.T, cfg.hidden), dtype=np.float32))
+    got = run_layer(cfg, b, w, x, 516)
+    kp, vp = wl.prior_kv_concat(cfg, b, 516)
+    exp = oracle.layer_step(cfg.as_dict(), b.n_new, b.ctx_len, x, w, kp, vp)
+    rows = np.arange(b.T)
+    check_layer(cfg, b, got, exp, rows, "few rows", staged_attention(cfg, b, x, w, kp, vp, rows),
+                x=x)
+    check_pool_rows(cfg, b, got, exp.k_new, exp.v_new, rows)
 
 
 def gemm_plans(cfg, T):
