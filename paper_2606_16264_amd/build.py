@@ -13,7 +13,8 @@ BUILD = os.path.join(ROOT, "_build", "mx")
 LIB = os.path.join(PKG, "libmx.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["mx_abi.cpp", "elementwise.hip", "attention.hip", "gemm.hip", "gemm_stream.hip"]
+SOURCES = ["mx_abi.cpp", "elementwise.hip", "attention.hip", "gemm.hip", "gemm_once.hip",
+           "gemm_stream.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-fvisibility=hidden",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument", "-I", os.path.join(ROOT, "include"), "-I", CSRC]

@@ -34,7 +34,6 @@ namespace mx {
 namespace {
 
 constexpr int kBufferWord3 = 0x00020000;  // raw buffer descriptor, 32-bit data format
-constexpr int kNonTemporal = 2;           // cache policy: streamed
 
 constexpr int kWaves = 4, kDepth = 8;
 

@@ -109,8 +109,11 @@ __device__ __forceinline__ u32x4 lds_read16_at(unsigned addr) {
   asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "i"(OFF));
   return v;
 }
+// (POLICY: 0, or kNonTemporal for data that is read once)
+constexpr int kNonTemporal = 2;
+template <int POLICY = 0>
 __device__ __forceinline__ void dma16(const void* g, unsigned lds_addr) {
-  __builtin_amdgcn_global_load_lds(g, (MX_LDS void*)(size_t)lds_addr, 16, 0, 0);
+  __builtin_amdgcn_global_load_lds(g, (MX_LDS void*)(size_t)lds_addr, 16, 0, POLICY);
 }
 
 // Request record uploaded by the host planner.

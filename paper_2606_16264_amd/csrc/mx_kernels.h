@@ -145,6 +145,13 @@ inline void set_b_tiled(GemmArgs& g) {
 constexpr int kStreamMaxM = 16;
 hipError_t launch_gemm_stream(const GemmArgs& args, hipStream_t stream);
 
+// The tiled GEMM with tile rows BM >= M (64 x 128, 128 x 256 or 256 x 256 tiles:
+// has_gemm_once), weights read once; ksplit > 1 leaves the fp32 planes at
+// args.partial.
+bool has_gemm_once(int BM, int BN);
+hipError_t launch_gemm_once(const GemmArgs& args, int BM, int ksplit, hipStream_t stream);
+hipError_t gemm_once_init();
+
 // Chooses a tile shape and split for the problem; ws_floats is the fp32
 // scratch available at args.partial.  A K split never needs more than
 // kMaxSplitFloats of scratch (256 MB: enough for a three-way split of the

@@ -89,6 +89,16 @@ def test_gemm_kernels_have_no_lds_read_hazard(tmp_path):
 
 
 @pytest.mark.skipif(not HAVE_HIPCC, reason="hipcc not available")
+def test_read_once_gemm_kernels_have_no_lds_read_hazard(tmp_path):
+    out = build.device_asm("gemm_once.hip", str(tmp_path / "gemm_once.s"))
+    res = {k: v for k, v in check(open(out).read()).items() if "gemm_once_kernel" in k}
+    # three tile shapes x (four epilogues + the split-K partial store)
+    assert len(res) == 15, sorted(res)
+    bad = {k: v[:3] for k, v in res.items() if v}
+    assert not bad, bad
+
+
+@pytest.mark.skipif(not HAVE_HIPCC, reason="hipcc not available")
 def test_attention_kernels_have_no_lds_read_hazard(tmp_path):
     out = build.device_asm("attention.hip", str(tmp_path / "attention.s"))
     res = {k: v for k, v in check(open(out).read()).items() if "_kernel" in k}

@@ -397,6 +397,15 @@ def test_gemm_few_rows(M, N, K, epi):
     gemm_case(M, N, K, epi, b_tiled=True)
 
 
+# The read-once kernels (M in one row of tiles, weights of at least 16 MB): every tile shape they
+# have at its edges of M, with a ragged last column tile, with and without a K split
+@pytest.mark.parametrize("tile_cfg,M", [(3, 17), (3, 64), (1, 65), (1, 128), (0, 129), (0, 256)])
+@pytest.mark.parametrize("N,K,epi,ksplit", [(8256, 1024, 2, 1), (4112, 2112, 1, 1),
+                                            (4112, 2112, 1, 5), (8192, 1024, 0, 1)])
+def test_gemm_read_once(tile_cfg, M, N, K, epi, ksplit):
+    gemm_case(M, N, K, epi, tile_cfg=tile_cfg, ksplit=ksplit, b_tiled=True)
+
+
 # N not a multiple of 4: the element-wise split-K reduce (plain and residual)
 @pytest.mark.parametrize("tile_cfg", [0, 3])
 @pytest.mark.parametrize("M,N,K,epi,ksplit", [(131, 1090, 512, 1, 2), (70, 775, 1024, 0, 4)])
