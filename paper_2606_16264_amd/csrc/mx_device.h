@@ -116,6 +116,17 @@ __device__ __forceinline__ void dma16(const void* g, unsigned lds_addr) {
   __builtin_amdgcn_global_load_lds(g, (MX_LDS void*)(size_t)lds_addr, 16, 0, POLICY);
 }
 
+// dma16 from a wave-uniform base and a 32-bit byte offset per lane: the
+// instruction's own addressing (the builtin forms a 64-bit address per lane
+// instead, a vector instruction and two registers per copy).  It writes m0, which
+// the compiler does not track: a kernel uses either this or dma16, and nothing
+// else that goes through m0.
+__device__ __forceinline__ void dma16_at(const void* base, unsigned off, unsigned lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr),
+               "v"(off), "s"(base)
+               : "memory");
+}
+
 // Request record uploaded by the host planner.
 struct ReqDev {
   int32_t tok_start;  // first row of the request in the batch
