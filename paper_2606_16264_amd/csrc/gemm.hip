@@ -142,12 +142,26 @@ struct Shape {
 // keep the model from choosing it.
 constexpr Shape kShapes[] = {{256, 256, 3.471, 0.02443, 1, 44.3},
                              {128, 256, 0.978, 0.01544, 1, 56.7},
-                             {128, 128, 0.615, 0.0115, 1, 45.7},
+                             {128, 128, 2.5, 0.0194, 2, 45.7},
                              {64, 128, 0.0, 0.00729, 1, 55.7},
                              {128, 256, 0.978, 0.0287, 1, 50.0}};
 constexpr int kNumShapes = 5;
 constexpr int kFeedMaxM = 256;  // rows up to which the feed estimate is used
 constexpr double kCUs = 256.0;
+// Two 128x128 workgroups share a CU; one alone takes 0.75 of the pair's time
+// (1003 x 4096 x 4096, 256 tiles: 53 us; 1003 x 6144 x 4096, 384 tiles, one pair on
+// half of the CUs: 71).  Priced as two rounds of single tiles, O of a 1003-token
+// 8B prompt ran 128x128 tiles, 54 us, not 128x256 split in two, 47 with the reduce
+// (the layer 447 -> 436 us).
+constexpr double kLoneUnit = 0.75;
+// One round of 128x256 tiles over at most 1024 rows takes 0.94 of what their
+// rounds take in larger problems: 400 x 4096 x 14336 split in four 61.5 us (256x256
+// split in eight 69.8), 576 x 10240 x 8192 unsplit 101 (256x256 split in two 107), 400
+// x 4096 x 4096 in four 30.8 (64x128 unsplit 35.3).  Without the limits the 13B
+// shape's down projection at 2176 rows, in whole rounds and a tail, took 284 us
+// instead of 261.
+constexpr double kOneRound = 0.94;
+constexpr int kOneRoundMaxM = 1024;
 
 // Estimated time (us) of one GEMM launch with tile shape c and K split ks, in
 // two regimes, or a negative value when the choice is not allowed.  Few rows
@@ -179,8 +193,11 @@ double estimate(int c, int ks, int M, int N, int K) {
     const double t_feed = per_cu * unit_bytes / (kShapes[c].feed_gbs * 1e3);
     return std::max(t_feed, 2.0 * N * K / 8.2e6) + 5.76 + (ks > 1 ? 0.222 * split_mb + 0.39 : 0.0);
   }
-  const double rounds = std::ceil(tiles * ks / (kCUs * kShapes[c].per_cu));
-  const double t_units = rounds * (kShapes[c].a_us + kShapes[c].b_us_per_k * k_unit);
+  const double per_cu = std::ceil(tiles * ks / kCUs);  // tile-units of the busiest CU
+  const double full = std::floor(per_cu / kShapes[c].per_cu);
+  const double rounds = full + (per_cu > full * kShapes[c].per_cu ? kLoneUnit : 0.0);
+  const double one = c == 1 && per_cu == 1.0 && M <= kOneRoundMaxM ? kOneRound : 1.0;
+  const double t_units = one * rounds * (kShapes[c].a_us + kShapes[c].b_us_per_k * k_unit);
   const double t_mem = 2.0 * ((double)N * K + (double)M * K) / hbm * 1e6;
   return std::max(t_units, t_mem) + (ks > 1 ? 0.197 * split_mb + 3.39 : 0.0);
 }

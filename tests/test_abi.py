@@ -194,6 +194,18 @@ def test_debug_gemm_tiled_errors(args, status):
     assert st == getattr(mx, status), st
 
 
+@pytest.mark.parametrize("problem,cfg,ksplit", [
+    ((1003, 4096, 4096), 1, 2), ((1024, 4096, 4096), 1, 2), ((400, 4096, 4096), 1, 4),
+    ((400, 4096, 14336), 1, 4), ((576, 10240, 8192), 1, 1), ((2176, 5120, 13824), 0, 1)])
+def test_gemm_plan_of_mid_sizes(problem, cfg, ksplit):
+    """The fastest measured plans of projections of a few hundred to a thousand rows, on whose
+    choice the prices of a lone 128 x 128 unit per CU and of one round of 128 x 256 tiles bear,
+    and of one past the row limit of the latter."""
+    M = problem[0]
+    p = mx.mx_debug_gemm_plan(*problem)
+    assert (p["cfg"], p["ksplit"], p["m_main"]) == (cfg, ksplit, M)
+
+
 def test_misaligned_pointers_rejected_before_device_work():
     cfg = wl.CONFIGS["c1"]
     c = mx_cfg(mx, cfg, 64)
