@@ -495,16 +495,23 @@ mx_status device_state(DeviceState** out) {
 // A staging buffer is rewritten or freed only after the event recorded behind
 // the last kernel that read it has completed.
 // Records the open group's event after its last upload (buffer `last`) on the
-// group's stream; every buffer of the group is then covered by it.
+// group's stream; every buffer of the group is then covered by it.  Buffers whose
+// event cannot be recorded are given up (never written or freed again): nothing
+// would tell when their kernels are done.
 hipError_t close_group(DeviceState* ds, int last) {
   hipError_t e = hipEventRecord(ds->ev[last], ds->group_stream);
-  if (e != hipSuccess) return e;
   for (int j = ds->group_first;; j = (j + 1) % DeviceState::kRing) {
-    ds->cover[j] = last;
+    if (e == hipSuccess) {
+      ds->cover[j] = last;
+    } else {
+      ds->buf[j] = ds->dbuf[j] = nullptr;
+      ds->cap[j] = 0;
+      ds->used[j] = false;
+    }
     if (j == last) break;
   }
   ds->group_first = -1;
-  return hipSuccess;
+  return e;
 }
 
 // Rotary inverse frequencies theta^(-2 k / d), k < d / 2 (the last pair of
@@ -591,17 +598,20 @@ mx_status staged(size_t bytes, hipStream_t stream, Pack&& pack, Launch&& launch)
     ds->cap[i] = cap;
   }
   pack((char*)ds->buf[i]);
-  e = launch(ds->dbuf[i]);
-  if (e != hipSuccess) return hip_fail(e, "metadata launch");
+  // from here on the kernel may read the buffer, also where launch reports an
+  // error (of the timing events around it, for one): the buffer joins a group first
   ds->used[i] = true;
   if (ds->group_first < 0) {
     ds->group_first = i;
     ds->group_stream = stream;
   }
+  const hipError_t launched = launch(ds->dbuf[i]);
   const int size = i - ds->group_first + 1;
-  if (stream != nullptr || size == DeviceState::kEvery || i == DeviceState::kRing - 1) {
-    if ((e = close_group(ds, i)) != hipSuccess) return hip_fail(e, "hipEventRecord");
-  }
+  e = hipSuccess;
+  if (stream != nullptr || size == DeviceState::kEvery || i == DeviceState::kRing - 1)
+    e = close_group(ds, i);
+  if (launched != hipSuccess) return hip_fail(launched, "metadata launch");
+  if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
   return MX_OK;
 }
 

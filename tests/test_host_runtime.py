@@ -1,0 +1,96 @@
+"""CPU tests of what libmx's host code asks of the HIP runtime: which kernels a
+call launches, and when a pinned staging buffer is written again.  The calls run
+in a process of their own with a stand-in runtime preloaded (fake_hip.cpp), which
+records launches and events and runs no kernel, so device pointers are made up."""
+import json
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = """
+import ctypes, json, sys, threading, time
+import numpy as np
+import paper_2606_16264_amd as mx
+fake = ctypes.CDLL(FAKE)
+fake.fake_log.restype = ctypes.c_char_p
+fake.fake_guard.argtypes = [ctypes.c_size_t]
+A = lambda i: ctypes.c_void_p(0x10000000 * (i + 1))   # a device address
+BIG = 1 << 40
+def log():
+    return [l.split() for l in fake.fake_log().decode().splitlines()]
+def batch(decodes, prefill=0):
+    n = decodes + (prefill > 0)
+    need = [3] * decodes + ([-(-prefill // 16)] if prefill else [])
+    at = np.cumsum([0] + need)
+    pages = np.arange(at[-1], dtype=np.int32)
+    return mx.Batch([mx.MX_DECODE] * decodes + [mx.MX_PREFILL] * (prefill > 0),
+                    [1] * decodes + [prefill] * (prefill > 0), [40] * decodes + [0] * (prefill > 0),
+                    [pages[at[i]:at[i + 1]] for i in range(n)])
+def step(b, cfg, stream=None):
+    return mx.lib().mx_layer_step(b.ptr, ctypes.byref(cfg), A(0), A(1), A(2), A(3), A(4), A(5), BIG,
+                                  stream)
+def append(b, shape, stream=None):
+    return mx.lib().mx_kv_append(b.ptr, ctypes.byref(shape), A(0), A(1), A(2), A(3), A(5), BIG,
+                                 stream)
+def attn(b, shape, stream=None):
+    return mx.lib().mx_paged_attn(b.ptr, ctypes.byref(shape), A(0), A(1), A(2), A(3), A(5), BIG,
+                                  stream)
+cfg = mx.layer_cfg(256, 512, 4, 4, 64, 1 << 20)
+"""
+
+
+@pytest.fixture(scope="session")
+def fake_hip(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake") / "libfakehip.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-Wall", "-o", so,
+                    os.path.join(HERE, "fake_hip.cpp"), "-ldl"], check=True)
+    return so
+
+
+def run(fake_hip, code, timeout=240):
+    """The JSON that `code`, run on the stand-in runtime, prints last."""
+    src = f"FAKE = {fake_hip!r}\n" + PRELUDE + textwrap.dedent(code)
+    out = subprocess.run([sys.executable, "-c", src], cwd=ROOT, capture_output=True, text=True,
+                         timeout=timeout, env={**os.environ, "LD_PRELOAD": fake_hip})
+    assert out.returncode == 0, out.stderr[-3000:]
+    return json.loads(out.stdout.strip().splitlines()[-1])
+
+
+def test_staging_buffers_outlive_their_readers(fake_hip):
+    """Calls of every entry point that stages, on the null stream and others in turn."""
+    r = run(fake_hip, """
+        for i in range(60):
+            s = [None, None, None, A(30), None, A(31)][i % 6]
+            b = batch(3, 20 + i)
+            st = [step(b, cfg, s), append(b, cfg.attn, s), attn(b, cfg.attn, s)]
+            assert st == [0, 0, 0], (i, st, mx.last_error())
+        print(json.dumps(dict(launches=len(log()), bad=fake.fake_violations())))
+        """)
+    assert r["launches"] >= 60 * 8 and r["bad"] == 0, r
+
+
+@pytest.mark.parametrize("stream", ["None", "A(30)"])
+def test_staging_buffer_of_a_call_that_fails_behind_its_launch(fake_hip, stream):
+    """The event record behind a launch that reads a staging buffer fails (launch timing's own,
+    or the ring's): the call reports it, and the buffer, which its kernel may still read, is not
+    written again by later calls."""
+    r = run(fake_hip, f"""
+        bad = []
+        for timing in (1, 0):
+            mx.mx_profile_enable(timing)
+            fake.fake_fail_record_behind(b"prologue_kernel")
+            st = [step(batch(3), cfg, {stream})]
+            st += [append(batch(3), cfg.attn, {stream}) for _ in range(20)]
+            bad.append([st, fake.fake_violations()])
+        print(json.dumps(bad))
+        """)
+    for st, violations in r:
+        assert violations == 0, r
+    assert r[0][0] == [6] + [0] * 20, r       # MX_ERR_HIP, then the calls go on
+    assert r[1][0].count(6) <= 1 and len(r[1][0]) == 21, r
