@@ -94,3 +94,48 @@ def test_staging_buffer_of_a_call_that_fails_behind_its_launch(fake_hip, stream)
         assert violations == 0, r
     assert r[0][0] == [6] + [0] * 20, r       # MX_ERR_HIP, then the calls go on
     assert r[1][0].count(6) <= 1 and len(r[1][0]) == 21, r
+
+
+def test_calls_plan_side_by_side(fake_hip):
+    """While one thread is still packing the metadata of a large batch (its staging buffer lets
+    the first write wait), a call of another thread on another stream goes through; the large
+    one follows when it may write."""
+    r = run(fake_hip, """
+        fake.fake_guard(1 << 20)
+        small, large = batch(3), batch(3, 200000)
+        assert step(small, cfg, A(30)) == 0     # first call: device state, a buffer
+        st = {}
+        def call(name, b, s):
+            st[name] = step(b, cfg, s)
+        t1 = threading.Thread(target=call, args=("large", large, A(31)), daemon=True)
+        t1.start()
+        while not fake.fake_guard_hit():
+            time.sleep(0.001)
+        t2 = threading.Thread(target=call, args=("small", small, A(30)), daemon=True)
+        t2.start()
+        t2.join(20)
+        during = dict(st)
+        fake.fake_guard_release()
+        t1.join(60)
+        t2.join(60)
+        print(json.dumps(dict(during=during, end=st, bad=fake.fake_violations())))
+        """)
+    assert r["during"] == {"small": 0}, r
+    assert r["end"] == {"small": 0, "large": 0} and r["bad"] == 0, r
+
+
+def test_staging_ring_under_threads(fake_hip):
+    """More threads than the ring has buffers, on the null stream and streams of their own."""
+    r = run(fake_hip, """
+        bad = []
+        def work(t):
+            for i in range(40):
+                s = None if t % 3 == 0 else A(30 + t)
+                st = append(batch(2 + t, 50 * (i % 5)), cfg.attn, s)
+                if st: bad.append((t, i, st, mx.last_error()))
+        ts = [threading.Thread(target=work, args=(t,)) for t in range(12)]
+        [t.start() for t in ts]
+        [t.join() for t in ts]
+        print(json.dumps(dict(bad=bad, launches=len(log()), violations=fake.fake_violations())))
+        """)
+    assert r == dict(bad=[], launches=480, violations=0), r
