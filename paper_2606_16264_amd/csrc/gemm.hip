@@ -313,14 +313,25 @@ hipError_t run(const GemmArgs& a, int ksplit, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// Whether a GEMM of one row of tiles over weights that come from HBM runs in the
+// read-once kernels.  Weights of less than 16 MB may well be in the caches (a tiny
+// GEMM, 132 x 1024 x 256, took 9.0 us with the deep ring against 7.7).  A K split's
+// fp32 planes go out to the caches and back meanwhile, and beside many of them the
+// non-temporal reads lose more than they save: the read-once kernels take 0.72-0.98
+// of the ordinary ones' time unsplit, 0.87-0.97 on average with planes of up to 0.15
+// of the weights' bytes, 1.0-1.1 beyond (every tile shape; 8192 x 28672 at 256 rows
+// split in eight, 0.14, 112 us against 129; 6144 x 4096 at 64 rows split in five,
+// 0.16, 18.1 against 16.4; 10240 x 8192 at 256 rows split in six, 0.37, 71 against 60).
+bool reads_once(int M, int N, int K, int BM, int ksplit) {
+  return M <= BM && (int64_t)N * K * 2 >= (int64_t)16 << 20 &&
+         (ksplit == 1 || (int64_t)40 * ksplit * M <= (int64_t)3 * K);
+}
+
 // reduce = false: a K split leaves its fp32 planes at a.partial for the caller
 // to reduce.
 template <int BM, int BN, int WM, int WN, int NS>
 hipError_t run_shape(const GemmArgs& a, int ksplit, bool reduce, hipStream_t stream) {
-  // one row of tiles over weights that come from HBM: the read-once kernels
-  // (weights of less than 16 MB may well be in the caches, and a tiny GEMM, 132 x
-  // 1024 x 256, took 9.0 us with the deep ring against 7.7)
-  const bool once = a.M <= BM && (int64_t)a.N * a.K * 2 >= (int64_t)16 << 20 && has_gemm_once(BM, BN);
+  const bool once = has_gemm_once(BM, BN) && reads_once(a.M, a.N, a.K, BM, ksplit);
   if (ksplit > 1) {
     hipError_t e = once ? launch_gemm_once(a, BM, ksplit, stream)
                         : run<BM, BN, WM, WN, NS, EPI_STORE, true>(a, ksplit, stream);

@@ -406,6 +406,14 @@ def test_gemm_read_once(tile_cfg, M, N, K, epi, ksplit):
     gemm_case(M, N, K, epi, tile_cfg=tile_cfg, ksplit=ksplit, b_tiled=True)
 
 
+# The same with K splits whose planes are small beside the weights, which is where they run split:
+# 129 K chunks in uneven splits, at the largest split of each row count
+@pytest.mark.parametrize("tile_cfg,M,ksplit", [(3, 17, 8), (3, 64, 8), (1, 65, 7), (1, 128, 4),
+                                               (0, 129, 3), (0, 256, 2)])
+def test_gemm_read_once_split(tile_cfg, M, ksplit):
+    gemm_case(M, 1040, 8256, 1, tile_cfg=tile_cfg, ksplit=ksplit, b_tiled=True)
+
+
 # N not a multiple of 4: the element-wise split-K reduce (plain and residual)
 @pytest.mark.parametrize("tile_cfg", [0, 3])
 @pytest.mark.parametrize("M,N,K,epi,ksplit", [(131, 1090, 512, 1, 2), (70, 775, 1024, 0, 4)])

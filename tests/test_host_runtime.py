@@ -139,3 +139,33 @@ def test_staging_ring_under_threads(fake_hip):
         print(json.dumps(dict(bad=bad, launches=len(log()), violations=fake.fake_violations())))
         """)
     assert r == dict(bad=[], launches=480, violations=0), r
+
+
+GEMMS = """
+def gemm_kernels(M, N, K, epi, tile_cfg=-1, ksplit=0):
+    log()
+    st = mx.lib().mx_debug_gemm_tiled(M, N, K, A(0), A(20), A(40), A(60), epi, tile_cfg, ksplit,
+                                      A(80), BIG, None)
+    assert st == 0, mx.last_error()
+    return [l[0] for l in log()]
+"""
+
+
+READ_ONCE = [  # tile shape, M, N, K, K split, whether the read-once kernel runs
+    # one row of tiles over 16 MB of weights or more, unsplit
+    (3, 64, 12288, 4096, 1, True), (1, 128, 12288, 4096, 1, True), (0, 256, 12288, 4096, 1, True),
+    (3, 65, 12288, 4096, 1, False), (3, 64, 2048, 4032, 1, False), (2, 64, 12288, 4096, 1, False),
+    # split: planes (4 ksplit M N bytes) of up to 0.15 of the weights (2 N K bytes)
+    (3, 64, 6144, 4096, 4, True), (3, 64, 6144, 4096, 5, False), (3, 61, 6144, 4096, 5, True),
+    (3, 62, 6144, 4096, 5, False), (1, 68, 5120, 5120, 8, False), (1, 128, 24576, 8192, 4, True),
+    (1, 128, 24576, 8192, 5, False), (0, 256, 8192, 28672, 8, True), (0, 256, 10240, 8192, 6, False)]
+
+
+def test_read_once_kernels_by_size(fake_hip):
+    """Which main-loop kernel a forced tile shape and K split run."""
+    r = run(fake_hip, GEMMS + f"""
+print(json.dumps([gemm_kernels(M, N, K, 0, c, ks) for c, M, N, K, ks, _ in {READ_ONCE!r}]))
+""")
+    for case, names in zip(READ_ONCE, r):
+        assert len(names) == 1 + (case[4] > 1), (case, names)
+        assert ("gemm_once_kernel" in names[0]) == case[5], (case, names)
