@@ -331,7 +331,8 @@ bool reads_once(int M, int N, int K, int BM, int ksplit) {
 // to reduce.
 template <int BM, int BN, int WM, int WN, int NS>
 hipError_t run_shape(const GemmArgs& a, int ksplit, bool reduce, hipStream_t stream) {
-  const bool once = has_gemm_once(BM, BN) && reads_once(a.M, a.N, a.K, BM, ksplit);
+  // (they stand for the four-stage shapes: the three-stage one runs as itself)
+  const bool once = NS == 4 && has_gemm_once(BM, BN) && reads_once(a.M, a.N, a.K, BM, ksplit);
   if (ksplit > 1) {
     hipError_t e = once ? launch_gemm_once(a, BM, ksplit, stream)
                         : run<BM, BN, WM, WN, NS, EPI_STORE, true>(a, ksplit, stream);

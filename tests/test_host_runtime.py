@@ -169,3 +169,16 @@ print(json.dumps([gemm_kernels(M, N, K, 0, c, ks) for c, M, N, K, ks, _ in {READ
     for case, names in zip(READ_ONCE, r):
         assert len(names) == 1 + (case[4] > 1), (case, names)
         assert ("gemm_once_kernel" in names[0]) == case[5], (case, names)
+
+
+def test_forced_shapes_run_as_themselves(fake_hip):
+    """Shape 4, 128 x 256 tiles through a three-stage ring, is not taken over by the four-stage
+    read-once kernel of the same tile."""
+    r = run(fake_hip, GEMMS + """
+print(json.dumps([gemm_kernels(M, 12288, 4096, 0, c, 1)[0] for c, M in
+                  ((0, 257), (1, 129), (2, 100), (3, 65), (4, 128), (4, 129))]))
+""")
+    shapes = ["256ELi256ELi128ELi64ELi4", "128ELi256ELi64ELi64ELi4", "128ELi128ELi64ELi64ELi4",
+              "64ELi128ELi32ELi64ELi4", "128ELi256ELi64ELi64ELi3", "128ELi256ELi64ELi64ELi3"]
+    for name, shape in zip(r, shapes):
+        assert f"gemm_kernelILi{shape}E" in name and "once" not in name, (name, shape)
