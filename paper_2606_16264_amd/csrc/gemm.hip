@@ -258,17 +258,18 @@ Plan plan_uncached(int M, int N, int K) {
     }
   }
   // ... unless the rows are one round of 256 x 256 tiles that leaves CUs free: its
-  // tiles have the chip's power and memory paths to themselves and take 0.65 of a
-  // full round's time with a quarter of the CUs at work, 0.73 with 0.7, 0.85 with
-  // 0.94, where estimate() prices a full round.  Taken a little higher (against the
-  // two parts' prices, which are estimates too): of 1500 row splits and their whole
-  // rounds measured, the choice is 0.4% above the best on average, 1.3% without
-  // this (608 x 15360 x 5120, 180 tiles: 92 us whole, 108 as 512 + 96 rows; 768 x
-  // 12288 x 4096, 144 tiles: 76 and 88).
+  // tiles have the chip's power and memory paths to themselves and take less than the
+  // full round that estimate() prices: with 0.55-0.8 of the CUs at work 0.69-0.75 of
+  // it on one card and 0.76-0.83 on another, more power-bound one, against 0.87 and
+  // 0.89 of their prices for the row splits.  At 0.84 the choice is 1.1 and 1.0% above
+  // the better of the two on average (317 and 348 problems measured on each), always
+  // splitting 5.2 and 0.9%, never splitting 2.4 and 6.0% (608 x 15360 x 5120, 180
+  // tiles: 92 us whole on the first card, 108 as 512 + 96 rows; 768 x 12288 x 4096, 144
+  // tiles: 76 and 88).
   const double tiles = (double)((M + 255) / 256) * ((N + 255) / 256);
   if (best.m_main < M && tiles <= kCUs) {
     const double t = estimate(0, 1, M, N, K);
-    if (t > 0.0 && t * (0.65 + 0.3 * tiles / kCUs) < best_t) best = {0, 1, M, -1, 0};
+    if (t > 0.0 && 0.84 * t < best_t) best = {0, 1, M, -1, 0};
   }
   return best;
 }
