@@ -154,14 +154,13 @@ constexpr double kCUs = 256.0;
 // 8B prompt ran 128x128 tiles, 54 us, not 128x256 split in two, 47 with the reduce
 // (the layer 447 -> 436 us).
 constexpr double kLoneUnit = 0.75;
-// One round of 128x256 tiles over at most 1024 rows takes 0.94 of what their
-// rounds take in larger problems: 400 x 4096 x 14336 split in four 61.5 us (256x256
-// split in eight 69.8), 576 x 10240 x 8192 unsplit 101 (256x256 split in two 107), 400
-// x 4096 x 4096 in four 30.8 (64x128 unsplit 35.3).  Without the limits the 13B
-// shape's down projection at 2176 rows, in whole rounds and a tail, took 284 us
-// instead of 261.
+// One round of 128x256 tiles takes 0.94 of what their rounds take in larger
+// problems (its tiles have the chip's power and memory paths to themselves for
+// their last part): 400 x 4096 x 14336 split in four 61.5 us (256x256 split in eight
+// 69.8), 576 x 10240 x 8192 unsplit 101 (256x256 split in two 107), 400 x 4096 x 4096
+// in four 30.8 (64x128 unsplit 35.3), 1028 x 4096 x 4096 unsplit 47.7 (256x256 split in
+// three 52.7), 2048 x 4096 x 11008 unsplit 144 (256x256 split in two 159).
 constexpr double kOneRound = 0.94;
-constexpr int kOneRoundMaxM = 1024;
 
 // Estimated time (us) of one GEMM launch with tile shape c and K split ks, in
 // two regimes, or a negative value when the choice is not allowed.  Few rows
@@ -196,7 +195,7 @@ double estimate(int c, int ks, int M, int N, int K) {
   const double per_cu = std::ceil(tiles * ks / kCUs);  // tile-units of the busiest CU
   const double full = std::floor(per_cu / kShapes[c].per_cu);
   const double rounds = full + (per_cu > full * kShapes[c].per_cu ? kLoneUnit : 0.0);
-  const double one = c == 1 && per_cu == 1.0 && M <= kOneRoundMaxM ? kOneRound : 1.0;
+  const double one = c == 1 && per_cu == 1.0 ? kOneRound : 1.0;
   const double t_units = one * rounds * (kShapes[c].a_us + kShapes[c].b_us_per_k * k_unit);
   const double t_mem = 2.0 * ((double)N * K + (double)M * K) / hbm * 1e6;
   return std::max(t_units, t_mem) + (ks > 1 ? 0.197 * split_mb + 3.39 : 0.0);

@@ -200,10 +200,20 @@ def test_debug_gemm_tiled_errors(args, status):
 def test_gemm_plan_of_mid_sizes(problem, cfg, ksplit):
     """The fastest measured plans of projections of a few hundred to a thousand rows, on whose
     choice the prices of a lone 128 x 128 unit per CU and of one round of 128 x 256 tiles bear,
-    and of one past the row limit of the latter."""
+    and of one that neither changes."""
     M = problem[0]
     p = mx.mx_debug_gemm_plan(*problem)
     assert (p["cfg"], p["ksplit"], p["m_main"]) == (cfg, ksplit, M)
+
+
+@pytest.mark.parametrize("problem,cfg,ksplit", [
+    ((1025, 4096, 4096), 1, 1), ((1152, 4096, 4096), 1, 1), ((2048, 4096, 11008), 1, 1),
+    ((2048, 2048, 9728), 1, 2)])
+def test_gemm_plan_of_one_round_past_1024_rows(problem, cfg, ksplit):
+    """The price of one round of 128 x 256 tiles holds at any row count (these plans are 8-13%
+    faster than the K splits of 256 x 256 tiles that a limit of 1024 rows had)."""
+    p = mx.mx_debug_gemm_plan(*problem)
+    assert (p["cfg"], p["ksplit"], p["m_main"]) == (cfg, ksplit, problem[0])
 
 
 @pytest.mark.parametrize("problem,whole", [
