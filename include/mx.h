@@ -330,8 +330,8 @@ mx_status mx_debug_gemm_tiled(int32_t M, int32_t N, int32_t K, const uint16_t* A
  * plan[2] < M the remaining rows run as a second GEMM after the first, with
  * tile shape plan[3] and K split plan[4] (plan[2] == M: one launch, plan[3] = -1).
  * K must be a multiple of 64.  (Up to 16 rows in the layer's operand layouts run in the
- * weight-streaming kernel, whatever the plan says.)  For tests that must know which path
- * a shape takes. */
+ * weight-streaming kernel, without scratch, where that is priced below the plan.)  For
+ * tests that must know which path a shape takes. */
 mx_status mx_debug_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t plan[5]);
 /* A forced row split with the operands in the layer's layouts (as
  * mx_debug_gemm_tiled): rows [0, m_main) with tile shape main_cfg and no K split,

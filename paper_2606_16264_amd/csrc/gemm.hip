@@ -229,11 +229,12 @@ struct Plan {
   int cfg, ksplit;
   int m_main;
   int tail_cfg, tail_ksplit;
+  double t;  // estimated time (us) of a plan without a row split
 };
 
 Plan plan_uncached(int M, int N, int K) {
   const Pick whole = choose_one(M, N, K);
-  Plan best{whole.cfg, whole.ksplit, M, -1, 0};
+  Plan best{whole.cfg, whole.ksplit, M, -1, 0, whole.t};
   if (M <= 2 * kFeedMaxM) return best;
   double best_t = whole.t;
   // first part: whole rounds of one tile shape without a K split; second part:
@@ -252,7 +253,7 @@ Plan plan_uncached(int M, int N, int K) {
       const double t = t_main + tail.t + 4.0;
       if (t < best_t * 0.97) {
         best_t = t;
-        best = {c, 1, j * BM, tail.cfg, tail.ksplit};
+        best = {c, 1, j * BM, tail.cfg, tail.ksplit, 0.0};
       }
     }
   }
@@ -268,7 +269,7 @@ Plan plan_uncached(int M, int N, int K) {
   const double tiles = (double)((M + 255) / 256) * ((N + 255) / 256);
   if (best.m_main < M && tiles <= kCUs) {
     const double t = estimate(0, 1, M, N, K);
-    if (t > 0.0 && 0.84 * t < best_t) best = {0, 1, M, -1, 0};
+    if (t > 0.0 && 0.84 * t < best_t) best = {0, 1, M, -1, 0, t};
   }
   return best;
 }
@@ -469,13 +470,31 @@ hipError_t launch_plan(const GemmArgs& a, const Plan& p, bool reduce, hipStream_
 }  // namespace
 
 namespace {
-// Few rows in the layer's layouts stream the weights (gemm_stream.hip, with both
-// sides measured).  Whole 64-column groups keep the paired epilogues' strips
-// inside N; strips are addressed with 32-bit byte offsets.
+// Estimated time (us) of the streaming kernel (gemm_stream.hip): its workgroups read
+// whole strips of the weights, so a number of them that leaves CUs out, or out of a
+// last round, or a long K for a few of them, costs what a K split of the tiles fills;
+// and every strip reads the activations again, up to as many bytes as the weights.
+// Fitted to 521 cold problems of 1 to 16 rows (N 1024-57344, K 2048-28672), 7.7% off
+// each on average.
+double stream_estimate(int M, int N, int K, bool paired) {
+  const double strips = paired ? 2 : 1, weights = strips * 32.0 * K;  // bytes of a workgroup
+  const double bytes = weights + 0.42 * M * 2.0 * K;
+  const double units = N / (16.0 * strips), r = units / kCUs, full = std::floor(r);
+  const double rounds = full + (r > full ? 0.57 + 0.43 * (r - full) : 0.0);
+  return std::max({rounds * bytes / 33.1e3, bytes / 65.5e3, units * weights / 7.14e6}) + 4.04;
+}
+
+// Few rows in the layer's layouts stream the weights where that is faster.  Whole
+// 64-column groups keep the paired epilogues' strips inside N; strips are addressed
+// with 32-bit byte offsets.  The plans' prices are low at so few rows: against 1.15 of
+// them the choice is 0.9% above the best measured on average, always streaming 4.4%,
+// never 15% (16 rows: 13B down 38 us streamed, 27 in tiles, 70B qkv 38 and 31, 7B down
+// 18.5 and 20.7; one row: 70B qkv 33.6 and 29.3, 13B qkv 25.3 and 28.4).
 bool streams(const GemmArgs& a) {
   const bool paired = a.epilogue == EPI_SWIGLU || a.epilogue == EPI_QKV;
   return a.M <= kStreamMaxM && a.a_tiled && a.b_row == 32 && a.N % (paired ? 64 : 16) == 0 &&
-         a.K <= (1 << 24);
+         a.K <= (1 << 24) &&
+         stream_estimate(a.M, a.N, a.K, paired) <= 1.15 * plan_gemm(a.M, a.N, a.K).t;
 }
 }  // namespace
 
@@ -485,7 +504,7 @@ hipError_t launch_gemm_config(const GemmArgs& a, size_t ws_floats, int cfg, int 
   if (cfg < 0 && streams(a)) return launch_gemm_stream(a, stream);
   Plan p = plan_gemm(a.M, a.N, a.K);
   if (cfg >= 0 && cfg < kNumShapes) {
-    p = Plan{cfg, ksplit >= 1 ? ksplit : 1, a.M, -1, 0};
+    p = Plan{cfg, ksplit >= 1 ? ksplit : 1, a.M, -1, 0, 0.0};
     if (a.K / BK < p.ksplit) return hipErrorInvalidValue;
   }
   return launch_plan(a, fit_scratch(p, a.M, a.N, ws_floats), true, stream);
@@ -498,7 +517,7 @@ hipError_t launch_gemm_rows(const GemmArgs& a, size_t ws_floats, int m_main, int
       tail_cfg >= kNumShapes || tail_ksplit < 1 || a.K / BK < tail_ksplit)
     return hipErrorInvalidValue;
   if ((a.a_tiled || a.c_tiled) && m_main % 16) return hipErrorInvalidValue;
-  const Plan p{cfg, 1, m_main, tail_cfg, tail_ksplit};
+  const Plan p{cfg, 1, m_main, tail_cfg, tail_ksplit, 0.0};
   if (plan_scratch(p, a.M, a.N) > ws_floats) return hipErrorInvalidValue;
   return launch_plan(a, p, true, stream);
 }

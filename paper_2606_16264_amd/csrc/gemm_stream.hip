@@ -1,6 +1,7 @@
-// gemm_stream.hip -- the projections of a few rows (M <= kStreamMaxM = 16): the
-// weights stream from HBM once and bound the time, so nothing is shared through
-// LDS and no K split leaves the kernel.  Operands in the layer's own layouts
+// gemm_stream.hip -- the projections of a few rows (M <= kStreamMaxM = 16, where
+// streams() in gemm.hip prices it below the tiled kernels): the weights stream from
+// HBM once and bound the time, so nothing is shared through LDS and no K split
+// leaves the kernel.  Operands in the layer's own layouts
 // (packed weights and activations in 16 x 32 tiles of 1 KB), where one load
 // instruction of a wave reads one whole tile in the register layout of
 // v_mfma_f32_16x16x32_bf16.
@@ -17,11 +18,13 @@
 //  - The product is taken transposed (weights as the A operand): a lane holds
 //    four consecutive columns of one token, one 8-byte store.
 //
-// Measured with cold weights, against the tiled kernels at their best K split
-// with its reduce (one row; 16 rows are the same): 7B qkv 23.8 -> 20.1 us, o 13.3 ->
-// 9.1, gate/up 38.6 -> 33.7, down 25.0 -> 18.9; 13B qkv 33.1 -> 33.4, o 16.1 -> 16.1;
-// 70B qkv 35.5 -> 36.8, gate/up 164 -> 146 (6.4 TB/s), down 85.3 -> 84.4.  Eight waves
-// per workgroup or a depth of 16 are slower wherever the strips do not fill the
+// Measured with cold weights in the layer, one row and 16, against the tiled kernels
+// with their K split's reduce: 7B qkv 26.1 -> 21.8 and 28.0 -> 24.4 us, gate/up 39.7 ->
+// 31.8 and 42.1 -> 33.8, down 21.7 -> 17.5 and 22.8 -> 20.3; 8B qkv 19.5 -> 12.3 and 17.2
+// -> 14.0; 70B o 25.7 -> 23.1.  Where the strips do not fill the CUs evenly, or at 16
+// rows over a long K, the tiles win and run instead: 70B qkv 36.3 against 34.4 at one
+// row, 40.7 against 34.2 at 16, 13B down 31.5 against 28.3 and 40.3 against 29.6.  Eight
+// waves per workgroup or a depth of 16 are slower wherever the strips do not fill the
 // CUs evenly (7B qkv 24.2, 13B qkv 42.8), a shallower ring at large K (70B qkv 44).
 // Two activation tiles per step (17-32 rows) cost 5-10 us more each and lose to
 // the tiled kernels, whose LDS tile reads the activations once per 128 rows (13B

@@ -182,3 +182,24 @@ print(json.dumps([gemm_kernels(M, 12288, 4096, 0, c, 1)[0] for c, M in
               "64ELi128ELi32ELi64ELi4", "128ELi256ELi64ELi64ELi3", "128ELi256ELi64ELi64ELi3"]
     for name, shape in zip(r, shapes):
         assert f"gemm_kernelILi{shape}E" in name and "once" not in name, (name, shape)
+
+
+STREAM = [  # N, K, epilogue, the row counts of 1, 8 and 16 that stream
+    (12288, 4096, 2, (1, 8, 16)), (4096, 4096, 1, (1, 8, 16)), (4096, 11008, 1, (1, 8, 16)),
+    (6144, 4096, 2, (1, 8, 16)), (15360, 5120, 2, (1, 8, 16)), (2048, 4096, 1, (1, 8, 16)),
+    (10240, 8192, 2, ()), (5120, 13824, 1, ()), (1024, 12288, 2, ()),
+    # the sizes of the streaming kernel's own tests
+    (48, 64, 0, (1, 8, 16)), (112, 1088, 1, (1, 8, 16)), (192, 64, 2, (1, 8, 16)),
+    (320, 1152, 2, (1, 8, 16)), (16, 4160, 0, (1, 8, 16)), (4160, 512, 1, (1, 8, 16))]
+
+
+def test_streaming_kernel_by_size(fake_hip):
+    """Which GEMMs of up to 16 rows stream the weights, and that more rows never do."""
+    r = run(fake_hip, GEMMS + f"""
+out = []
+for N, K, epi, _ in {STREAM!r}:
+    out.append([M for M in (1, 8, 16, 17) if "stream" in gemm_kernels(M, N, K, epi)[0]])
+print(json.dumps(out))
+""")
+    for case, rows in zip(STREAM, r):
+        assert tuple(rows) == case[3], (case, rows)
