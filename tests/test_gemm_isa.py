@@ -4,6 +4,7 @@ registers those reads land in.  These tests compile the library's kernels to
 gfx950 assembly (on the CPU) and check that no instruction touches the
 destination of an LDS read that may still be in flight."""
 import os
+import re
 import shutil
 
 import pytest
@@ -105,3 +106,18 @@ def test_attention_kernels_have_no_lds_read_hazard(tmp_path):
     assert len(res) == 4, sorted(res)
     bad = {k: v[:3] for k, v in res.items() if v}
     assert not bad, bad
+
+
+@pytest.mark.skipif(not HAVE_HIPCC, reason="hipcc not available")
+def test_attention_copies_alone_use_m0(tmp_path):
+    """The prefill tiles' copies set m0 from inline assembly, which the compiler does not track:
+    every copy has its own write, with the wait state between, and nothing else touches m0."""
+    out = build.device_asm("attention.hip", str(tmp_path / "attention.s"))
+    ops = [l.split(";")[0].strip() for l in open(out)]
+    ops = [l for l in ops if l and not l.startswith(".") and not l.endswith(":")]
+    uses = [i for i, l in enumerate(ops) if re.search(r"\bm0\b", l)]
+    copies = [i for i, l in enumerate(ops) if l.startswith("global_load_lds")]
+    assert copies and [i + 2 for i in uses] == copies
+    for i in uses:
+        assert re.fullmatch(r"s_mov_b32 m0, s\d+", ops[i]) and ops[i + 1] == "s_nop 0", ops[i:i + 3]
+        assert re.fullmatch(r"global_load_lds_dwordx4 v\d+, s\[\d+:\d+\]", ops[i + 2]), ops[i + 2]

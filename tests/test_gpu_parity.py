@@ -702,7 +702,7 @@ MEDIUM_MHA = wl.LayerConfig("medium-mha", 1536, 2816, 12, 12, 128)
 
 def test_layer_step_split_reduces_all_rows():
     """A 90-row batch of a 1536-wide layer on which every projection is split
-    over K (QKV three ways, gate/up four, down seven: 44 K chunks in uneven
+    over K (QKV three ways, O six, gate/up two, down seven: 44 K chunks in uneven
     splits), so every split reduce runs: the QKV one with RoPE and the KV
     append, the SwiGLU one, the residual one, and the output projection's
     reduce fused with the residual and the second RMSNorm.  Every row of every
@@ -711,6 +711,8 @@ def test_layer_step_split_reduces_all_rows():
     cfg = MEDIUM_MHA
     rng = np.random.default_rng(17)
     b = wl.custom_batch(rng, rng.integers(8, 300, size=60), [(30, 0)])
+    plans = gemm_plans(cfg, b.T)
+    assert all(p["ksplit"] > 1 and p["m_main"] == b.T for p in plans.values()), plans
     w = small_weights(rng, cfg)
     x = wl.f32_to_bf16_bits(rng.standard_normal((b.T, cfg.hidden), dtype=np.float32))
     got = run_layer(cfg, b, w, x, 2929)
@@ -719,6 +721,38 @@ def test_layer_step_split_reduces_all_rows():
     rows = np.arange(b.T)
     check_layer(cfg, b, got, exp, rows, cfg.name, staged_attention(cfg, b, x, w, kp, vp, rows), x=x)
     check_pool_rows(cfg, b, got, exp.k_new, exp.v_new, rows)
+
+
+# Layers whose QKV projection runs unsplit in the read-once kernels (one row of tiles over 16 MB
+# of weights): 64 x 128 tiles, then 128 x 256 and 256 x 256 ones, which take many heads
+READ_ONCE_QKV = [(wl.LayerConfig("once-64", 512, 256, 64, 32, 128), 3, [(37, 3), (19, 21)]),
+                 (wl.LayerConfig("once-128", 256, 256, 192, 48, 128), 1, [(56, 7), (41, 26), (15, 3)]),
+                 (wl.LayerConfig("once-256", 256, 256, 192, 48, 128), 0, [(129, 5), (69, 18)])]
+
+
+@pytest.mark.parametrize("cfg,tile_cfg,chunks", READ_ONCE_QKV, ids=lambda v: getattr(v, "name", None))
+def test_layer_step_read_once_qkv(cfg, tile_cfg, chunks):
+    """The QKV epilogue (rotary embedding and both cache writes) of the read-once kernels, which
+    the debug entry points do not reach: row counts that are no multiple of 16, chunks that start
+    anywhere in a page.  Every row and every new slot is checked, and no pool entry outside the
+    new slots may change."""
+    say(f"case: layer step read-once QKV {cfg.name}")
+    rng = np.random.default_rng(97)
+    b = wl.custom_batch(rng, [9, 30, 100, 17, 250], chunks)
+    plan = gemm_plans(cfg, b.T)["qkv"]
+    assert (plan["cfg"], plan["ksplit"], plan["m_main"]) == (tile_cfg, 1, b.T) and b.T % 16
+    assert cfg.qkv_rows * cfg.hidden * 2 >= 16 << 20
+    w = small_weights(rng, cfg)
+    x = wl.f32_to_bf16_bits(rng.standard_normal((b.T, cfg.hidden), dtype=np.float32))
+    got = run_layer(cfg, b, w, x, 4747, keep_before=True)
+    kp, vp = wl.prior_kv_concat(cfg, b, 4747)
+    exp = oracle.layer_step(cfg.as_dict(), b.n_new, b.ctx_len, x, w, kp, vp)
+    rows = np.arange(b.T)
+    check_layer(cfg, b, got, exp, rows, cfg.name, staged_attention(cfg, b, x, w, kp, vp, rows), x=x)
+    check_pool_rows(cfg, b, got, exp.k_new, exp.v_new, rows)
+    written = set(oracle.token_map(b.n_new, b.ctx_len, b.page_tables, 16).tok_slot.tolist())
+    assert changed_slots(got["k0"], got["k"], False) <= written
+    assert changed_slots(got["v0"], got["v"], True) <= written
 
 
 def test_layer_step_streams_and_ring():
