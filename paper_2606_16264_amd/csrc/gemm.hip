@@ -331,14 +331,13 @@ hipError_t run(const GemmArgs& a, int ksplit, hipStream_t stream) {
 // read-once kernels.  Weights of less than 16 MB may well be in the caches (a tiny
 // GEMM, 132 x 1024 x 256, took 9.0 us with the deep ring against 7.7).  A K split's
 // fp32 planes go out to the caches and back meanwhile, and beside many of them the
-// non-temporal reads lose more than they save: the read-once kernels take 0.72-0.98
-// of the ordinary ones' time unsplit, 0.87-0.97 on average with planes of up to 0.15
-// of the weights' bytes, 1.0-1.1 beyond (every tile shape; 8192 x 28672 at 256 rows
-// split in eight, 0.14, 112 us against 129; 6144 x 4096 at 64 rows split in five,
-// 0.16, 18.1 against 16.4; 10240 x 8192 at 256 rows split in six, 0.37, 71 against 60).
+// non-temporal reads gain nothing: in the layer step (four layer shapes, 23 row counts
+// from 17 to 256, cold weights) the read-once kernels take 0.77-0.95 of the ordinary
+// ones' time unsplit, 0.86-1.03 with planes of up to a quarter of the weights' bytes,
+// 0.98-1.05 beyond (8B qkv at 72 rows split in eight, 0.28, 26.0 us against 24.8).
 bool reads_once(int M, int N, int K, int BM, int ksplit) {
   return M <= BM && (int64_t)N * K * 2 >= (int64_t)16 << 20 &&
-         (ksplit == 1 || (int64_t)40 * ksplit * M <= (int64_t)3 * K);
+         (ksplit == 1 || (int64_t)8 * ksplit * M <= K);
 }
 
 // reduce = false: a K split leaves its fp32 planes at a.partial for the caller

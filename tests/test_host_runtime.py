@@ -155,10 +155,10 @@ READ_ONCE = [  # tile shape, M, N, K, K split, whether the read-once kernel runs
     # one row of tiles over 16 MB of weights or more, unsplit
     (3, 64, 12288, 4096, 1, True), (1, 128, 12288, 4096, 1, True), (0, 256, 12288, 4096, 1, True),
     (3, 65, 12288, 4096, 1, False), (3, 64, 2048, 4032, 1, False), (2, 64, 12288, 4096, 1, False),
-    # split: planes (4 ksplit M N bytes) of up to 0.15 of the weights (2 N K bytes)
-    (3, 64, 6144, 4096, 4, True), (3, 64, 6144, 4096, 5, False), (3, 61, 6144, 4096, 5, True),
-    (3, 62, 6144, 4096, 5, False), (1, 68, 5120, 5120, 8, False), (1, 128, 24576, 8192, 4, True),
-    (1, 128, 24576, 8192, 5, False), (0, 256, 8192, 28672, 8, True), (0, 256, 10240, 8192, 6, False)]
+    # split: planes (4 ksplit M N bytes) of up to a quarter of the weights (2 N K bytes)
+    (3, 64, 6144, 4096, 8, True), (3, 64, 6144, 4032, 8, False), (1, 102, 6144, 4096, 5, True),
+    (1, 103, 6144, 4096, 5, False), (1, 104, 15360, 5120, 4, True), (1, 72, 6144, 4096, 8, False),
+    (0, 256, 8192, 28672, 8, True), (0, 170, 10240, 8192, 6, True), (0, 171, 10240, 8192, 6, False)]
 
 
 def test_read_once_kernels_by_size(fake_hip):
