@@ -166,15 +166,28 @@ def summarize_traffic(fetch_csv, write_csv, commands_txt, workload, out_json,
 
 
 def source_sha(rel):
+    """Hash of a kernel source and the headers beside it that it includes,
+    directly or through each other (the GEMM's tile is in one)."""
     import hashlib
-    with open(os.path.join(ROOT, rel), "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+    import re
+    folder, todo, seen, h = os.path.dirname(rel), [os.path.basename(rel)], set(), hashlib.sha256()
+    while todo:
+        name = todo.pop()
+        path = os.path.join(ROOT, folder, name)
+        if name in seen or not os.path.exists(path):
+            continue
+        seen.add(name)
+        with open(path, "rb") as f:
+            text = f.read()
+        h.update(text)
+        todo += sorted(re.findall(r'^#include "(.+)"', text.decode(), re.M))
+    return h.hexdigest()
 
 
 def measured_traffic(kernel, workload, source):
     """HBM bytes per launch of `kernel` on `workload` from the committed
     rocprofv3 counter summary (profiles/traffic_<kernel>_<workload>.json), or
-    None when there is none or the kernel source changed since it was taken."""
+    None when there is none or the kernel's sources changed since it was taken."""
     path = os.path.join(ROOT, "profiles", f"traffic_{kernel}_{workload}.json")
     if not os.path.exists(path):
         return None

@@ -142,6 +142,29 @@ def test_committed_traffic_summaries_are_consistent():
         assert rec["algorithmic_bytes_per_launch"] == int(parts[part]["bytes"])
 
 
+@pytest.mark.parametrize("tag", sorted(bench.TRAFFIC_TAGS))
+def test_measured_traffic_needs_the_sources_it_was_taken_from(tag, tmp_path, monkeypatch):
+    """A summary counts until its kernel's source or a header with a part of the
+    kernel changes (the GEMM's tile, the device helpers)."""
+    import shutil
+    source = bench.TRAFFIC_TAGS[tag][1]
+    folder = os.path.dirname(source)
+    shutil.copytree(os.path.join(ROOT, folder), tmp_path / folder,
+                    ignore=shutil.ignore_patterns("*.so", "*.o"))
+    (tmp_path / "profiles").mkdir()
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    rec = {"hbm_bytes_per_launch": 7, "source_sha256": bench.source_sha(source)}
+    (tmp_path / "profiles" / f"traffic_{tag}_w.json").write_text(json.dumps(rec))
+    assert bench.measured_traffic(tag, "w", source) == 7
+    headers = ["mx_device.h"] + ["gemm_tile.h"] * tag.startswith("gemm")
+    for name in [os.path.basename(source)] + headers:
+        path = tmp_path / folder / name
+        text = path.read_text()
+        path.write_text(text + "\n// changed\n")
+        assert bench.measured_traffic(tag, "w", source) is None, name
+        path.write_text(text)
+
+
 def test_too_few_predictor_batches_are_refused_before_any_gpu_work():
     r = run_bench("--predictor", "4")
     assert r.returncode != 0
