@@ -173,7 +173,9 @@ mx_status mx_pack_weights(const mx_layer_cfg* cfg, const mx_layer_weights* canon
  * v_pool's transposed page layout.  A pure byte copy: the pools are bit-equal
  * to what a plain copy would leave.  Errors as every entry point: host checks
  * first (MX_ERR_NULL for a NULL tensor, MX_ERR_INVALID for a misaligned one,
- * MX_ERR_TOO_LARGE for a short workspace), nothing enqueued on error.
+ * MX_ERR_TOO_LARGE for a short workspace), nothing enqueued on error.  The
+ * workspace is checked as for mx_paged_attn but not written: the copy reads its
+ * runs from the library's own staging.
  */
 mx_status mx_kv_append(const mx_batch* batch, const mx_attn_shape* shape,
                        const uint16_t* k_new, const uint16_t* v_new, uint16_t* k_pool,

@@ -7,8 +7,8 @@
 //    sub-tile computed with v_mfma_f32_16x16x32_bf16 (one product per 16 x 16
 //    block and 32-wide K slice: under the chip's power limit it sustains a
 //    higher rate than the 32 x 32 x 16 form, for the same LDS reads);
-//  - K is consumed in 32-wide slices through an LDS ring (4 stages; 3 for the
-//    shape that puts two workgroups on a CU) filled by the DMA path
+//  - K is consumed in 32-wide slices through an LDS ring (4 stages, 3 in the last
+//    shape, 6 in the read-once 64 x 128 tiles) filled by the DMA path
 //    (global_load_lds): the other slices are in flight while the matrix cores
 //    work on one, and no registers are spent on staging;
 //  - B is addressed through block, row and K-slice strides: row-major, or the
@@ -139,7 +139,7 @@ struct Shape {
 // two workgroups per CU; with the 16 x 16 x 32 main loop a 128x256 wave needs
 // more than the 128 registers that four waves per SIMD leave, so it runs one
 // per CU, and its figures (a fourth stage missing against the 128x256 shape)
-// keep the model from choosing it.
+// keep the model from choosing it where it prices at all (see choose_one).
 constexpr Shape kShapes[] = {{256, 256, 3.471, 0.02443, 1, 44.3},
                              {128, 256, 0.978, 0.01544, 1, 56.7},
                              {128, 128, 2.5, 0.0194, 2, 45.7},
@@ -167,13 +167,16 @@ constexpr double kOneRound = 0.94;
 // (M <= kFeedMaxM): the layer's weights arrive cold from HBM and the busiest
 // CU's feed bounds the time: its tile-units (ceil(units / 256)) times the
 // bytes one unit streams (its A and B rows over its K slice) at the shape's
-// per-CU fetch rate, plus a fixed cost.  More rows: the busiest CU runs
-// ceil(units / (256 per_cu)) rounds of tile-units, and nothing beats
-// streaming the operands from HBM once.  A K split adds the fp32 partial round
-// trip and the reduce launch.  Both fitted on cold timings of the layer GEMMs
-// of the four layer shapes, every tile shape and every K split from 1 to 8.  Few
-// rows (15 GEMMs at 24, 40, 64, 96, 128, 160, 200 and 256 rows, one row of tiles
-// in its read-once kernels): the picks are 0.3% above the best measured on
+// per-CU fetch rate, plus a fixed cost; the weights' stream bounds it from below
+// (the 8.2e6 bytes per us of that bound belong to the fit with the fixed 5.76 us
+// beside them, and are no rate of the memory, which gives 6.7e6).  More rows: the
+// busiest CU's ceil(units / 256) units run in rounds of per_cu, a last single one
+// of a pair's shape at kLoneUnit of a round, and nothing beats streaming the
+// operands from HBM once.  A K split adds the fp32 partial round trip and the
+// reduce launch.  Both fitted on cold timings of the layer GEMMs of the four layer
+// shapes, every tile shape and every K split from 1 to 8.  Few rows (15 GEMMs at
+// 24, 40, 64, 96, 128, 160, 200 and 256 rows, timed with read-once kernels for
+// every single row of tiles): the picks are 0.3% above the best measured on
 // average, 5% at most (4.9% on average with the constants fitted before those
 // kernels).  More rows (320 to 3200): 0.8% on average.
 double estimate(int c, int ks, int M, int N, int K) {
@@ -206,7 +209,8 @@ struct Pick {
   double t;
 };
 
-// The best (tile shape, K split) of one launch over all M rows.
+// The best (tile shape, K split) of one launch over all M rows.  K below 256, which
+// estimate() does not price, runs the last shape.
 Pick choose_one(int M, int N, int K) {
   Pick best{kNumShapes - 1, 1, 1e30};
   for (int c = 0; c < kNumShapes; c++)

@@ -1,10 +1,11 @@
 // gemm_once.hip -- the tiled GEMM where M fits one tile, so that every weight is
 // read once: non-temporal weight copies, and for 64 x 128 tiles a ring of six
 // slices instead of four.  Such launches are bound by the weights' way from HBM.
-// Measured with cold weights (four-slice ring and ordinary copies before): 7B
-// gate/up at 64 rows 41.1 -> 34.9 us (38.0 with the ring alone), QKV unsplit 36.9
-// -> 31.1, split in two 27.0 -> 24.9, 13B gate/up at 128 rows 71.6 -> 65.7, 70B down
-// at 256 rows split in eight 141 -> 129, 70B gate/up 223 -> 219.
+// Measured with cold weights, each launch by itself (four-slice ring and ordinary
+// copies before): 7B gate/up at 64 rows 41.1 -> 34.9 us (38.0 with the ring alone),
+// QKV unsplit 36.9 -> 31.1, split in two 27.0 -> 24.9, 13B gate/up at 128 rows 71.6
+// -> 65.7, 70B gate/up at 256 rows 223 -> 219.  A K split with many planes gains
+// less in the layer than by itself; reads_once() in gemm.hip leaves it out.
 #include "gemm_tile.h"
 #include "mx_device.h"
 #include "mx_kernels.h"

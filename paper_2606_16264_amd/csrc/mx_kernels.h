@@ -141,13 +141,14 @@ inline void set_b_tiled(GemmArgs& g) {
 }
 
 // The GEMM of a few rows (M <= kStreamMaxM, A and B in their tile layouts, N % 16
-// == 0, N % 64 == 0 for the SwiGLU and QKV epilogues): streams the weights.
+// == 0, N % 64 == 0 for the SwiGLU and QKV epilogues): streams the weights.  The
+// plan runs it where it prices it below the tiled kernels.
 constexpr int kStreamMaxM = 16;
 hipError_t launch_gemm_stream(const GemmArgs& args, hipStream_t stream);
 
-// The tiled GEMM with tile rows BM >= M (64 x 128, 128 x 256 or 256 x 256 tiles:
-// has_gemm_once), weights read once; ksplit > 1 leaves the fp32 planes at
-// args.partial.
+// The tiled GEMM with tile rows BM >= M, weights read once (instantiated for the
+// four-stage 64 x 128, 128 x 256 and 256 x 256 tiles: has_gemm_once); ksplit > 1
+// leaves the fp32 planes at args.partial.
 bool has_gemm_once(int BM, int BN);
 hipError_t launch_gemm_once(const GemmArgs& args, int BM, int ksplit, hipStream_t stream);
 hipError_t gemm_once_init();

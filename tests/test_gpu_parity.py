@@ -407,7 +407,7 @@ def test_gemm_read_once(tile_cfg, M, N, K, epi, ksplit):
 
 
 # The same with K splits whose planes are small beside the weights, which is where they run split:
-# 129 K chunks in uneven splits, at the largest split of each row count
+# 129 K chunks, most of them in uneven splits
 @pytest.mark.parametrize("tile_cfg,M,ksplit", [(3, 17, 8), (3, 64, 8), (1, 65, 7), (1, 128, 4),
                                                (0, 129, 3), (0, 256, 2)])
 def test_gemm_read_once_split(tile_cfg, M, ksplit):
