@@ -56,8 +56,10 @@ def fake_hip(tmp_path_factory):
 def run(fake_hip, code, timeout=240):
     """The JSON that `code`, run on the stand-in runtime, prints last."""
     src = f"FAKE = {fake_hip!r}\n" + PRELUDE + textwrap.dedent(code)
+    # (behind what is preloaded already, such as a sanitizer's runtime)
+    preload = " ".join(filter(None, [os.environ.get("LD_PRELOAD"), fake_hip]))
     out = subprocess.run([sys.executable, "-c", src], cwd=ROOT, capture_output=True, text=True,
-                         timeout=timeout, env={**os.environ, "LD_PRELOAD": fake_hip})
+                         timeout=timeout, env={**os.environ, "LD_PRELOAD": preload})
     assert out.returncode == 0, out.stderr[-3000:]
     return json.loads(out.stdout.strip().splitlines()[-1])
 
