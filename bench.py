@@ -97,8 +97,8 @@ def summarize_stats(csv_path, command, workload, out_md):
              f"Workload: {workload_text(workload)}.  The run includes setup (weight packing, pool "
              "fill) and the per-kernel timing steps.", "",
              "Command (one MI355X):", "", "```", command, "```", "",
-             "Durations in microseconds (rocprofv3 kernel trace).  gemm_kernel<BM, BN, WM, WN, LDS stages, "
-             "epilogue, split>: epilogue 0 store, 1 residual, 2 SwiGLU, 3 QKV.", "",
+             "Durations in microseconds (rocprofv3 kernel trace).  gemm_kernel and gemm_once_kernel"
+             "<BM, BN, WM, WN, LDS stages, epilogue, split>: epilogue 0 store, 1 residual, 2 SwiGLU, 3 QKV.", "",
              "| kernel | calls | average us | min us | max us | share % |",
              "|---|---:|---:|---:|---:|---:|"]
     rows.sort(key=lambda r: -float(r["TotalDurationNs"]))
